@@ -199,27 +199,64 @@ constexpr double dp_ea(int l) {
   return t;
 }
 
+// The stage coefficients in constant memory, the non-zero (a a)_sl and a_sl of
+// stage s in the order the stage sums use them. An attempt reads them with a
+// dozen scalar loads, each issued a stage ahead of its use; written as literals
+// they took 90 scalar moves per attempt, which a wave alone on its SIMD (a
+// launch's longest rays) issues in its own time: two large frames in one launch
+// 72.0 -> 68.7 ms, 256 rays' integration 735 -> 679 us.
+struct StageCoef {
+  double v[6][12];
+};
+constexpr StageCoef stage_coef() {
+  StageCoef t{};
+  for (int s = 1; s < 7; ++s) {
+    int n = 0;
+    for (int l = 0; l < s; ++l) {
+      if (dp_aa(s, l) != 0.0) t.v[s - 1][n++] = dp_aa(s, l);
+      if (DP::A[s][l] != 0.0) t.v[s - 1][n++] = DP::A[s][l];
+    }
+  }
+  return t;
+}
+__constant__ StageCoef g_stage_coef = stage_coef();
+
 // One DP45 attempt. Inputs: state (x, v), A[0] = acceleration at the state.
 // Outputs: fifth-order state (xn, vn), A[6] = acceleration there, and the sum
-// of squared scaled errors (accept when <= 6, i.e. RMS <= 1).
+// of squared scaled errors (accept when <= 6, i.e. RMS <= 1). Components
+// whose acceleration is identically zero (all of the homogeneous radial-o
+// branch, z of azimuthal-e) keep their velocity and have no error: their
+// stage sums are left out (the same values without the products with zero:
+// ~30 of ~430 instructions of an azimuthal-e attempt, ~100 of ~110 of a
+// radial-o one).
 template <int KIND>
 __device__ __forceinline__ double dp45_attempt(double a, const double x[3],
                                                const double v[3], double A[7][3], double h,
                                                double rtol, double atol, double xn[3],
                                                double vn[3]) {
+  constexpr int NA = KIND == K_RO ? 0 : KIND == K_AE ? 2 : 3;  // components with an acceleration
+  typedef const StageCoef __attribute__((address_space(4))) *CoefPtr;
+  CoefPtr coef = (CoefPtr)&g_stage_coef;
+  asm volatile("" : "+s"(coef));  // keeps the loads in the attempt: ~90 scalar registers do not stay free across it
 #pragma unroll
   for (int s = 1; s < 7; ++s) {
     double X[3], V[3];
 #pragma unroll
-    for (int i = 0; i < 3; ++i) {
+    for (int i = 0; i < NA; ++i) {
       double ax = 0.0, av = 0.0;
+      int n = 0;
 #pragma unroll
       for (int l = 0; l < s; ++l) {
-        if (dp_aa(s, l) != 0.0) ax = fma(dp_aa(s, l), A[l][i], ax);
-        if (DP::A[s][l] != 0.0) av = fma(DP::A[s][l], A[l][i], av);
+        if (dp_aa(s, l) != 0.0) ax = fma(coef->v[s - 1][n++], A[l][i], ax);
+        if (DP::A[s][l] != 0.0) av = fma(coef->v[s - 1][n++], A[l][i], av);
       }
       V[i] = fma(h, av, v[i]);
       X[i] = fma(h, fma(h, ax, dp_c(s) * v[i]), x[i]);
+    }
+#pragma unroll
+    for (int i = NA; i < 3; ++i) {
+      V[i] = v[i];
+      X[i] = fma(h, dp_c(s) * v[i], x[i]);
     }
     accel<KIND>(a, X[0], X[1], V[0], V[1], V[2], A[s][0], A[s][1], A[s][2]);
     if (s == 6) {
@@ -227,17 +264,20 @@ __device__ __forceinline__ double dp45_attempt(double a, const double x[3],
       for (int i = 0; i < 3; ++i) { xn[i] = X[i]; vn[i] = V[i]; }
     }
   }
+  if constexpr (NA == 0) return 0.0;
   double e6[6], s6[6];
 #pragma unroll
   for (int i = 0; i < 3; ++i) {
-    double ex = 0.0, ev = 0.0;
+    if (i < NA) {
+      double ex = 0.0, ev = 0.0;
 #pragma unroll
-    for (int l = 0; l < 7; ++l) {
-      if (dp_ea(l) != 0.0) ex = fma(dp_ea(l), A[l][i], ex);
-      if (DP::E[l] != 0.0) ev = fma(DP::E[l], A[l][i], ev);
+      for (int l = 0; l < 7; ++l) {
+        if (dp_ea(l) != 0.0) ex = fma(dp_ea(l), A[l][i], ex);
+        if (DP::E[l] != 0.0) ev = fma(DP::E[l], A[l][i], ev);
+      }
+      e6[2 * i] = ex * (h * h);
+      e6[2 * i + 1] = ev * h;
     }
-    e6[2 * i] = ex * (h * h);
-    e6[2 * i + 1] = ev * h;
     s6[2 * i] = fma(rtol, fmax(fabs(x[i]), fabs(xn[i])), atol);
     s6[2 * i + 1] = fma(rtol, fmax(fabs(v[i]), fabs(vn[i])), atol);
   }
@@ -256,13 +296,13 @@ __device__ __forceinline__ double dp45_attempt(double a, const double x[3],
     for (int k = 4; k >= 0; --k) suf[k] = suf[k + 1] * s6[k + 1];
     const double r = rcp64(pre[5] * s6[5]);
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
+    for (int k = 0; k < 2 * NA; ++k) {
       const double q = e6[k] * (pre[k] * suf[k]) * r;
       sum = fma(q, q, sum);
     }
   } else {
 #pragma unroll
-    for (int k = 0; k < 6; ++k) {
+    for (int k = 0; k < 2 * NA; ++k) {
       const double q = e6[k] * rcp64(s6[k]);
       sum = fma(q, q, sum);
     }
@@ -274,16 +314,11 @@ __device__ __forceinline__ double dp45_attempt(double a, const double x[3],
 // to [0.2, 5]; evaluated in FP32 (a controller heuristic, not part of the
 // solution's accuracy)
 __device__ __forceinline__ double dp45_factor(double sum, bool after_reject) {
-  float fac;
-  if (sum == 0.0) fac = 5.0f;
-  else if (!(sum == sum)) fac = 0.2f;
-  else {
-    float rms2 = (float)(sum * (1.0 / 6.0));
-    fac = 0.9f * exp2f(-0.1f * log2f(rms2));
-    fac = fminf(5.0f, fmaxf(0.2f, fac));
-  }
-  if (after_reject && fac > 1.0f) fac = 1.0f;
-  return (double)fac;
+  // a zero sum gives exp2f(inf), clipped to 5; a NaN drops out of fmaxf: 0.2
+  const float rms2 = (float)(sum * (1.0 / 6.0));
+  float fac = 0.9f * exp2f(-0.1f * log2f(rms2));
+  fac = fminf(5.0f, fmaxf(0.2f, fac));
+  return (double)(after_reject ? fminf(fac, 1.0f) : fac);
 }
 
 // classical RK4 step for y = (x, v); A1 = acceleration at the state
@@ -779,24 +814,13 @@ __device__ __forceinline__ bool inside_open(const CloakP& c, const double x[3]) 
 // z - z1, z0 - z. |g| <= tol places the state within tol (1 + O(tol/b)) of
 // the boundary; no square root is needed, and dg/dh along a velocity v is
 // (x v_x + y v_y) / b (resp. -/a) or +-v_z.
-__device__ __forceinline__ double gsq(const CloakP& c, int id, const double x[3]) {
-  double r2 = fma(x[0], x[0], x[1] * x[1]);
-  switch (id) {
-    case B_SIDE: return (r2 - c.b2) * (0.5 / c.b);
-    case B_INNER: return (c.a2 - r2) * (0.5 / c.a);
-    case B_TOP: return x[2] - c.z1;
-    default: return c.z0 - x[2];
-  }
-}
-
-__device__ __forceinline__ double gsq_slope(const CloakP& c, int id, const double x[3], const double v[3]) {
-  double rv = fma(x[0], v[0], x[1] * v[1]);
-  switch (id) {
-    case B_SIDE: return rv * c.inv_b;
-    case B_INNER: return -rv * c.inv_a;
-    case B_TOP: return v[2];
-    default: return -v[2];
-  }
+// ka, kb = 1/(2a), 1/(2b).
+__device__ __forceinline__ void boundaries(const CloakP& c, double ka, double kb, const double x[3], double g[4]) {
+  const double r2 = fma(x[0], x[0], x[1] * x[1]);
+  g[B_SIDE] = (r2 - c.b2) * kb;
+  g[B_INNER] = (c.a2 - r2) * ka;
+  g[B_TOP] = x[2] - c.z1;
+  g[B_BOTTOM] = c.z0 - x[2];
 }
 
 // first entry of o + s d (s > 0) into r <= b, z0 <= z <= z1; surf B_SIDE /

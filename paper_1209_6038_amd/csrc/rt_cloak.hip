@@ -60,6 +60,17 @@ constexpr int MAX_BOUNCES = 64;
 constexpr long long REFL_CHUNK = 1LL << 22;  // samples per chunk with first-order reflections
 constexpr unsigned int FETCH_CHUNK = 64;  // rays claimed per wave per atomic
 constexpr int LONG_RAY_ATTEMPTS = 64;      // see the issue priority in k_transit
+// a wave with fewer live lanes than this makes its attempts with all 64: with
+// less than 16 lanes enabled, FP64 code of this length runs up to 3x slower
+// when the CU's other SIMDs run it too (4 waves of one block, one lane each:
+// 2.6 us per azimuthal-e attempt, against 0.81 us with 16 lanes or more)
+constexpr int FEW_LANES = 16;
+// attempts between refills where the options leave it open: 2^20 random rays
+// 700, 650, 635 and 637 us at 2, 4, 8 and 12, two large frames 72.9 and 69.0 ms
+// at 2 and 12, the 3-D render 3.31 ms at 2 and 4, 3.38 at 8 and 12
+constexpr int DEFAULT_REFILL = 4;
+constexpr int HOLD_SHARE = 64;             // see k_transit
+constexpr int DRAIN_PERIOD = 32;           // attempts between looks at the queue once it is exhausted
 constexpr int NBUCKET = 16;               // difficulty buckets
 constexpr int NBIN = NBUCKET * NSEG;       // sort keys: (segment, difficulty bucket)
 // the counting sort runs a fixed grid; each block owns one contiguous range of
@@ -104,6 +115,13 @@ __device__ __forceinline__ unsigned long long lanemask_lt() {
   return lane == 0 ? 0ull : ((~0ull) >> (64 - lane));
 }
 
+// the lanes where p holds, and whether there is one
+__device__ __forceinline__ unsigned long long lanes(bool p) { return __builtin_amdgcn_ballot_w64(p); }
+__device__ __forceinline__ bool any_lane(bool p) { return lanes(p) != 0ull; }
+
+// a value equal in all lanes of the wave, as a scalar
+__device__ __forceinline__ unsigned int uniform(unsigned int x) { return __builtin_amdgcn_readfirstlane(x); }
+
 // Block-aggregated append: this thread's index in the counter's range
 // (valid where `want`), with one global atomic per block instead of one per
 // wave. Every thread of the block must call it (it synchronizes); `sh` is
@@ -139,7 +157,7 @@ __device__ __forceinline__ SegMap seg_map(const Table &T) {
   SegMap m;
   m.off[0] = 0;
 #pragma unroll
-  for (int q = 0; q < NSEG; ++q) m.off[q + 1] = m.off[q] + T.ctr[C_N(q)];
+  for (int q = 0; q < NSEG; ++q) m.off[q + 1] = m.off[q] + uniform(T.ctr[C_N(q)]);
   return m;
 }
 
@@ -446,20 +464,43 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_scatter(Table T) {
   }
 }
 
+// The integrator's arguments, one struct at the start of its kernel argument
+// segment. What the step loop reads at every attempt is used from the kernel
+// parameter; what only refills, crossings and interfaces read is loaded again
+// there through cold_args(), whose pointer the compiler cannot see through: a
+// wave's ~100 scalar registers do not hold the 40-odd pointers and constants
+// beside the tableau's coefficients, and values kept across the loop would be
+// spilled to vector lanes or push the coefficients out of their registers.
+struct TransitArgs {
+  CloakP c;
+  OptsP o;
+  Table T;
+  int refill, simds;
+};
+__device__ __forceinline__ const TransitArgs *cold_args() {
+  const char __attribute__((address_space(4))) *p =
+      (const char __attribute__((address_space(4))) *)__builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return (const TransitArgs *)p;
+}
+
 // integrator state of one lane (lives in registers)
 struct Lane {
-  double x[3], v[3], A1[3];  // base state and its acceleration
-  double h, t;               // next step length, optical path so far
-  double lo, hi, ht;         // boundary search: bracket and trial length
-  int ns, bounces, rid, riter;
+  double x[3], v[3], A1[3];  // base state and (DP45) its acceleration
+  double h, t;               // next step length (boundary search: trial length), optical path so far
+  double lo, hi;             // boundary search: bracket
+  int ns, bounces, riter;
+  int mode;                  // what the lane does, see below
   bool after_reject;
   double wt;  // Eq. (12) weight (FRES only)
 };
+// Lane::mode: M_STEP, a boundary id (searching the crossing of that
+// boundary), M_AT + id (standing on boundary id, the interface not yet
+// applied), M_STOP + status (stopped, the slot not yet written) or M_IDLE
+// (no ray). Ordered so that each question the loop asks of all lanes is one
+// comparison.
+enum { M_STEP = -1, M_AT = 4, M_STOP = 8, M_IDLE = 16 };
 
-// One iteration of a lane of branch KIND: one attempt of the scheme from the
-// base state, then either the step controller (stepping) or one safeguarded
-// Newton update of the crossing length (rid >= 0: locating the crossing of
-// boundary rid). Returns the final status when the ray stops, else -1.
 // Eq. (12) at an interface event of branch KIND: the wave k = M v meets
 // boundary rid at x; transmitted fraction (.x) and same-type reflected
 // fraction (.y). Kept out of line, with scalar arguments: the events are rare
@@ -488,142 +529,198 @@ __device__ __noinline__ double2 fresnel_event(double kappa, double a, int rid, d
   return make_double2(Tt, Rr);
 }
 
-template <int KIND, bool HAM, bool FRES>
-__device__ __forceinline__ int iterate(Lane &L, const CloakP &c, const OptsP &o,
-                                       double tol, double &hr) {
-  if (L.rid < 0 && L.ns >= o.max_steps) return RT_RAY_MAXSTEPS;
-  const double hs = L.rid < 0 ? L.h : L.ht;
+// Iterations of the lanes of branch KIND: one attempt of the scheme from the
+// base state, then either the step controller (stepping) or one safeguarded
+// Newton update of the crossing length (mode >= 0: locating the crossing of
+// that boundary). What most attempts end with (an accepted step that stays
+// inside, a rejected step) is straight-line code, and while no lane of the
+// wave needs more the loop goes straight to the next attempt (up to
+// `budget` of them; returns how many were made). Everything else is behind that one wave-wide test: a
+// wave whose rays are all under way, above all one that holds the launch's
+// last long ray, issues the attempts and little more. Lanes that are not
+// `live` only go through the motions (see FEW_LANES); they change nothing that
+// is used again.
+template <int KIND, int SCH>
+__device__ __forceinline__ int advance(Lane &L, bool live, const CloakP &hot, const OptsP &o, int max_ns, double tol,
+                                       int budget) {
+  constexpr bool DP45 = SCH == RT_SCHEME_DP45, HAM = SCH == RT_SCHEME_RK4_HAM || SCH == RT_SCHEME_RK4_HAMC;
+  const bool step = live && L.mode < 0;
   double xn[3], vn[3];
-  double A[7][3];
-  double sum = 0.0;
-  double dts = hs;  // optical path of the attempt: its length but in the Hamiltonian form
-  if constexpr (HAM) {
-    // state (x, k); the step is in the ray parameter tau of the polynomial
-    // or (RT_SCHEME_RK4_HAMC) the canonically normalized Hamiltonian
-    if (o.scheme == RT_SCHEME_RK4_HAMC) rk4_ham_step<KIND, true>(c.a, c.kappa, L.x, L.v, hs, xn, vn, dts);
-    else rk4_ham_step<KIND, false>(c.a, c.kappa, L.x, L.v, hs, xn, vn, dts);
-  } else if (o.scheme == RT_SCHEME_RK4) {
-    rk4_step<KIND>(c.a, L.x, L.v, L.A1, hs, xn, vn);
-  } else {
+  double dts, hs;  // the attempt's optical path (its length but in the Hamiltonian form) and length
+  double dip = 0.0, dip_dd = 0.0, dip_pc2 = 0.0;  // radial-o: see below
+  bool acc, go_on, rare;
+  int done = 0;  // attempts made (equal in all lanes)
+  for (;;) {
+    double A[7][3];
+    double sum = 0.0;
+    hs = L.h;
+    dts = hs;
+    if constexpr (HAM) {
+      // state (x, k); the step is in the ray parameter tau of the polynomial
+      // or (RT_SCHEME_RK4_HAMC) the canonically normalized Hamiltonian
+      rk4_ham_step<KIND, SCH == RT_SCHEME_RK4_HAMC>(hot.a, hot.kappa, L.x, L.v, hs, xn, vn, dts);
+    } else if constexpr (!DP45) {
+      accel<KIND>(hot.a, L.x[0], L.x[1], L.v[0], L.v[1], L.v[2], A[0][0], A[0][1], A[0][2]);
+      rk4_step<KIND>(hot.a, L.x, L.v, A[0], hs, xn, vn);
+    } else {
 #pragma unroll
-    for (int i = 0; i < 3; ++i) A[0][i] = L.A1[i];
-    sum = dp45_attempt<KIND>(c.a, L.x, L.v, A, hs, o.rtol, o.atol, xn, vn);
-  }
-  if (L.rid < 0) {
-    // ---- stepping ----
-    ++L.ns;
-    if (o.scheme == RT_SCHEME_DP45) {
-      if (!(sum <= 6.0)) {
-        L.h *= dp45_factor(sum, false);
-        L.after_reject = true;
-        return (L.h >= 1e-12) ? -1 : RT_RAY_DIVERGED;
-      }
-      L.h = fmin(L.h * dp45_factor(sum, L.after_reject), o.hmax);
-      L.after_reject = false;
+      for (int i = 0; i < 3; ++i) A[0][i] = L.A1[i];
+      sum = dp45_attempt<KIND>(hot.a, L.x, L.v, A, hs, o.rtol, o.atol, xn, vn);
     }
-    if (!finite6(xn, vn)) return RT_RAY_DIVERGED;
-    if (inside_open(c, xn)) {
-      if constexpr (KIND == K_RO) {
-        // homogeneous medium (Eq. (14): eps_o = kappa): the step is a
-        // straight chord, which can dip into r < a and come back out
-        // within one step. If its closest approach to the axis lies inside,
-        // search the crossing before that point, starting from the chord's
-        // first root of |x + tau (xn - x)|_xy = a.
-        const double dx = xn[0] - L.x[0], dy = xn[1] - L.x[1];
-        const double dd = fma(dx, dx, dy * dy);
-        if (dd > 0.0) {
-          const double f = -fma(L.x[0], dx, L.x[1] * dy) / dd;
-          const double px = fma(f, dx, L.x[0]), py = fma(f, dy, L.x[1]);
-          const double pc2 = fma(px, px, py * py);
-          if (f > 0.0 && f < 1.0 && pc2 < c.a2) {
-            const double tau = f - sqrt((c.a2 - pc2) / dd);
-            L.rid = B_INNER;
-            L.lo = 0.0;
-            L.hi = f * hs;
-            L.ht = hs * fmin(fmax(tau, 1e-3 * f), (1.0 - 1e-3) * f);
-            L.riter = 0;
-            return -1;
-          }
+    // A position inside the material is finite. An accepted DP45 step has a
+    // finite velocity too: a non-finite one makes the last stage's
+    // acceleration, and with it the error sum, NaN (the homogeneous branch's
+    // velocity never changes).
+    bool keep = step && inside_open(hot, xn);
+    acc = true;
+    go_on = false;
+    if constexpr (DP45) {
+      acc = sum <= 6.0;
+      keep = keep && acc;
+      const double hr = hs * dp45_factor(sum, acc && L.after_reject);
+      const double hn = acc ? fmin(hr, o.hmax) : hr;
+      L.h = step ? hn : hs;
+      L.after_reject = !acc;  // (set again when a search ends)
+      go_on = step && !acc && L.h >= 1e-12;
+    } else {
+      keep = keep && isfinite(vn[0]) && isfinite(vn[1]) && isfinite(vn[2]);
+    }
+    if constexpr (KIND == K_RO) {
+      // homogeneous medium (Eq. (14): eps_o = kappa): the step is a straight
+      // chord, which can dip into r < a and come back out within one step:
+      // `dip`, the fraction of the chord at its closest approach to the
+      // axis, if that lies below r = a within the chord (the quotient is
+      // formed only for a lane that may)
+      const double dx = xn[0] - L.x[0], dy = xn[1] - L.x[1];
+      dip_dd = fma(dx, dx, dy * dy);
+      const double num = -fma(L.x[0], dx, L.x[1] * dy);
+      if (keep && num > 0.0 && num <= dip_dd) {
+        const double f = num / dip_dd;
+        const double px = fma(f, dx, L.x[0]), py = fma(f, dy, L.x[1]);
+        dip_pc2 = fma(px, px, py * py);
+        if (f > 0.0 && f < 1.0 && dip_pc2 < hot.a2) {
+          dip = f;
+          keep = false;
         }
       }
+    }
+    L.ns += step ? 1 : 0;
+    if (keep) {
 #pragma unroll
       for (int i = 0; i < 3; ++i) { L.x[i] = xn[i]; L.v[i] = vn[i]; }
       L.t += dts;
-      if constexpr (!HAM) {
-        if (o.scheme == RT_SCHEME_RK4) {
-          accel<KIND>(c.a, L.x[0], L.x[1], L.v[0], L.v[1], L.v[2], L.A1[0], L.A1[1], L.A1[2]);
-        } else {
+      if constexpr (DP45) {
 #pragma unroll
-          for (int i = 0; i < 3; ++i) L.A1[i] = A[6][i];
-        }
+        for (int i = 0; i < 3; ++i) L.A1[i] = A[6][i];
       }
-      return -1;
     }
+    go_on = go_on || keep;
+    rare = live && (!go_on || L.ns >= max_ns);  // the step budget: checked before a lane's next step
+    ++done;
+    if (any_lane(rare) || done >= budget) break;
+  }
+  if (!rare) return done;
+  bool at = false;  // the ray is on its boundary at (xn, vn)
+  int mode = L.mode;
+  if (go_on) {  // kept or rejected, the step budget spent
+    mode = M_STOP + RT_RAY_MAXSTEPS;
+  } else if ((step && !acc) || !finite6(xn, vn)) {  // the step collapsed
+    mode = M_STOP + RT_RAY_DIVERGED;
+  } else if (step) {
     // the step left the material: search the earliest crossing, starting
     // from the boundary with the smallest linearly interpolated fraction
     // -g0 / (g1 - g0) (compared as num * den' < num' * den, denominators
     // positive; one reciprocal for the winner: the fraction only seeds the
     // search)
+    const double kb = 0.5 * cold_args()->c.inv_b, ka = 0.5 * cold_args()->c.inv_a;
+    double g0[4], g1[4];
+    boundaries(hot, ka, kb, L.x, g0);
+    boundaries(hot, ka, kb, xn, g1);
     double bn = 2.0, bd = 1.0;
-    int rid = B_SIDE;
+    mode = B_SIDE;
 #pragma unroll
     for (int id = 0; id < 4; ++id) {
-      double g1 = gsq(c, id, xn);
-      if (g1 >= 0.0) {
-        double g0 = fmin(gsq(c, id, L.x), -1e-300);
-        double num = -g0, den = g1 - g0;
-        if (num * bd < bn * den) { bn = num; bd = den; rid = id; }
+      if (g1[id] >= 0.0) {
+        const double g = fmin(g0[id], -1e-300);
+        const double num = -g, den = g1[id] - g;
+        if (num * bd < bn * den) { bn = num; bd = den; mode = id; }
       }
     }
     const double best = bn * rcp64_1(bd);
-    L.rid = rid;
     L.lo = 0.0;
     L.hi = hs;
-    L.ht = hs * fmin(fmax(best, 1e-3), 1.0 - 1e-3);
+    L.h = hs * fmin(fmax(best, 1e-3), 1.0 - 1e-3);
     L.riter = 0;
-    return -1;
-  }
-  // ---- locating the crossing of boundary rid ----
-  if (!finite6(xn, vn)) return RT_RAY_DIVERGED;
-  double f = gsq(c, L.rid, xn);
-  ++L.riter;
-  if (!(fabs(f) <= tol || L.riter >= 100 || !(L.hi - L.lo > 1e-300))) {
-    if (f < 0.0) L.lo = L.ht; else L.hi = L.ht;
-    double slope;
-    if constexpr (HAM) {
-      // dg/dtau along dx/dtau at the trial point
-      double dx[3], dk[3], dt_;
-      if (o.scheme == RT_SCHEME_RK4_HAMC) ham_rhs_canon<KIND>(c.a, c.kappa, xn, vn, dx, dk, dt_);
-      else ham_rhs<KIND>(c.a, c.kappa, xn, vn, dx, dk, dt_);
-      slope = gsq_slope(c, L.rid, xn, dx);
-    } else {
-      slope = gsq_slope(c, L.rid, xn, vn);
+    if constexpr (KIND == K_RO) {
+      if (dip > 0.0) {
+        // search the crossing before the closest approach, starting from
+        // the chord's first root of |x + tau (xn - x)|_xy = a
+        const double tau = dip - sqrt((hot.a2 - dip_pc2) / dip_dd);
+        mode = B_INNER;
+        L.hi = dip * hs;
+        L.h = hs * fmin(fmax(tau, 1e-3 * dip), (1.0 - 1e-3) * dip);
+      }
     }
-    double hn = L.ht - f * rcp64_1(slope);
-    if (!(hn > L.lo && hn < L.hi)) hn = 0.5 * (L.lo + L.hi);
-    L.ht = hn;
-    return -1;
-  }
-  // an earlier crossing of another boundary takes precedence
-  int other = -1;
+  } else {
+    // locating the crossing of boundary mode
+    const double inv_b = cold_args()->c.inv_b, inv_a = cold_args()->c.inv_a;
+    double g[4];
+    boundaries(hot, 0.5 * inv_a, 0.5 * inv_b, xn, g);
+    const double f = mode < B_TOP ? (mode == B_SIDE ? g[B_SIDE] : g[B_INNER])
+                                  : (mode == B_TOP ? g[B_TOP] : g[B_BOTTOM]);
+    ++L.riter;
+    if (!(fabs(f) <= tol || L.riter >= 100 || !(L.hi - L.lo > 1e-300))) {
+      if (f < 0.0) L.lo = hs; else L.hi = hs;
+      double dx[3];  // direction along which the boundary function is followed
+      if constexpr (HAM) {
+        // dx/dtau at the trial point
+        double dk[3], dt_;
+        ham_rhs_any<KIND, SCH == RT_SCHEME_RK4_HAMC>(hot.a, hot.kappa, xn, vn, dx, dk, dt_);
+      } else {
 #pragma unroll
-  for (int id = 0; id < 4; ++id)
-    if (id != L.rid && gsq(c, id, xn) > tol) other = id;
-  if (other >= 0) {
-    L.rid = other;
-    L.lo = 0.0;
-    L.hi = L.ht;
-    L.ht = 0.5 * L.ht;
-    L.riter = 0;
-    return -1;
-  }
-  // the ray is on boundary rid at (xn, vn)
-  L.t += dts;
+        for (int i = 0; i < 3; ++i) dx[i] = vn[i];
+      }
+      const double rv = fma(xn[0], dx[0], xn[1] * dx[1]);
+      const double slope = mode < B_TOP ? (mode == B_SIDE ? rv * inv_b : -rv * inv_a)
+                                        : (mode == B_TOP ? dx[2] : -dx[2]);
+      double hn = hs - f * rcp64_1(slope);
+      if (!(hn > L.lo && hn < L.hi)) hn = 0.5 * (L.lo + L.hi);
+      L.h = hn;
+    } else {
+      // an earlier crossing of another boundary takes precedence
+      int other = -1;
 #pragma unroll
-  for (int i = 0; i < 3; ++i) { L.x[i] = xn[i]; L.v[i] = vn[i]; }
-  if constexpr (HAM) ham_convert<KIND>(c.a, c.kappa, L.x, L.v, false);  // k -> v
-  const int rid = L.rid;
-  L.rid = -1;
+      for (int id = 0; id < 4; ++id)
+        if (id != mode && g[id] > tol) other = id;
+      at = other < 0;
+      if (at) {
+        mode += M_AT;
+      } else {
+        mode = other;
+        L.lo = 0.0;
+        L.hi = hs;
+        L.h = 0.5 * hs;
+        L.riter = 0;
+      }
+    }
+  }
+  L.mode = mode;
+  if (at) {
+    L.t += dts;
+#pragma unroll
+    for (int i = 0; i < 3; ++i) { L.x[i] = xn[i]; L.v[i] = vn[i]; }
+    if constexpr (HAM) ham_convert<KIND>(hot.a, hot.kappa, L.x, L.v, false);  // k -> v
+  }
+  return done;
+}
+
+// The interface a lane stands on (mode = M_AT + boundary). Returns the final
+// status when the ray stops, else -1 (it goes on from the boundary point
+// after a reflection, the step controller restarted).
+template <int KIND, int SCH, bool FRES>
+__device__ __forceinline__ int interface_event(Lane &L, const CloakP &c, const OptsP &o, int max_ns, double &hr) {
+  constexpr bool HAM = SCH == RT_SCHEME_RK4_HAM || SCH == RT_SCHEME_RK4_HAMC;
+  const int rid = L.mode - M_AT;
   if (rid == B_INNER) {
     // optic axis along the mirror normal (radial cloak): one reflected ray
     if (!(c.mirror && (KIND == K_RO || KIND == K_RE) && L.bounces < o.max_bounces))
@@ -641,7 +738,6 @@ __device__ __forceinline__ int iterate(Lane &L, const CloakP &c, const OptsP &o,
     if (leaves) {
 #pragma unroll
       for (int i = 0; i < 3; ++i) L.v[i] = d[i];
-      L.rid = rid;  // the exit boundary, kept with the finished ray
       return RT_RAY_EXITED;  // the exit transmission is applied by the finish kernel
     }
     if (L.bounces >= o.max_bounces) return RT_RAY_TIR;
@@ -655,9 +751,11 @@ __device__ __forceinline__ int iterate(Lane &L, const CloakP &c, const OptsP &o,
   ++L.bounces;
   L.h = o.h0;
   L.after_reject = false;
+  L.mode = M_STEP;
   if constexpr (HAM) ham_convert<KIND>(c.a, c.kappa, L.x, L.v, true);  // v -> k
-  else accel<KIND>(c.a, L.x[0], L.x[1], L.v[0], L.v[1], L.v[2], L.A1[0], L.A1[1], L.A1[2]);
-  return -1;
+  else if constexpr (SCH == RT_SCHEME_DP45)
+    accel<KIND>(c.a, L.x[0], L.x[1], L.v[0], L.v[1], L.v[2], L.A1[0], L.A1[1], L.A1[2]);
+  return L.ns >= max_ns ? RT_RAY_MAXSTEPS : -1;
 }
 
 // Persistent integrator with in-line boundary events.
@@ -671,67 +769,100 @@ __device__ __forceinline__ int iterate(Lane &L, const CloakP &c, const OptsP &o,
 // reflection or the inner metal mirror (the ray continues from the boundary
 // point with the step controller restarted). Only this bookkeeping diverges;
 // the attempt itself is the same code for every lane of a branch.
+// Interfaces and stopped rays are handled together, once one in EVENT_SHARE of
+// the wave's rays waits for it or the wave is about to refill, and a refill
+// comes early once IDLE_LANES lanes are idle: a wave of 64 easy rays finishes
+// ~1.5 rays per attempt, so it passes through that code (~150 instructions, as
+// many again for a refill) every few attempts instead of at almost every one.
+// Two 4096^2 x 4 spp frames in one launch, refill period 12: 69.0 ms, with
+// shares of 16 and no early refill 70.8.
+//
 // Integrate the rays of segment `seg` (all of one branch, KIND) with the
 // calling wave until the segment's queue is drained and every lane of the
-// wave is idle. The wave claims chunks of FETCH_CHUNK queue positions with
-// one atomic each and refills its idle lanes every `refill` attempts. The
-// lane state lives here, specialized for the branch, so no code of another
-// branch is interleaved with the step loop.
-template <int KIND, bool HAM, bool FRES>
-__device__ __forceinline__ void run_segment(const CloakP &c, const OptsP &o, const Table &T, const SegMap &sm,
-                                            int seg, double tol, int refill,
-                                            unsigned int &drained) {
-  int slot = -1;
+// wave is idle. The wave starts on queue positions [cur, end), then claims
+// chunks of FETCH_CHUNK positions from `dyn` on with one atomic each (unless
+// it is to `hold`), and refills its idle lanes every `refill` attempts. The lane state lives here,
+// specialized for the branch, so no code of another branch is interleaved
+// with the step loop.
+constexpr int EVENT_SHARE = 8, IDLE_LANES = 8;
+template <int KIND, int SCH, bool FRES>
+__device__ __forceinline__ void run_segment(const CloakP &hot, const OptsP &hoto, int seg, unsigned int off,
+                                            unsigned int len, double tol, int refill, unsigned int cur,
+                                            unsigned int end, unsigned int dyn, bool hold, unsigned int &drained) {
+  constexpr bool HAM = SCH == RT_SCHEME_RK4_HAM || SCH == RT_SCHEME_RK4_HAMC;
+  const int max_ns = (int)(hoto.max_steps < 0x7fffffffLL ? hoto.max_steps : 0x7fffffffLL);
+  int slot = 0;
   Lane L;
-  L.h = 0.0; L.t = 0.0; L.lo = 0.0; L.hi = 0.0; L.ht = 0.0;
+  L.h = 0.0; L.t = 0.0; L.lo = 0.0; L.hi = 0.0;
   L.x[0] = L.x[1] = L.x[2] = 0.0; L.v[0] = L.v[1] = L.v[2] = 0.0; L.A1[0] = L.A1[1] = L.A1[2] = 0.0;
-  L.ns = 0; L.bounces = 0; L.rid = -1; L.riter = 0; L.after_reject = false;
-  // wave-private chunk [cur, end) of the queue; cur, end and drained are wave-uniform
-  unsigned int cur = 0, end = 0;
-  const unsigned int off = off_of(sm, seg), len = off_of(sm, seg + 1) - off;
+  L.ns = 0; L.bounces = 0; L.mode = M_IDLE; L.riter = 0; L.after_reject = false;
+  // wave-private range [cur, end) of the queue; cur, end and drained are wave-uniform
   for (;;) {
-    unsigned long long m = __ballot(slot < 0);
+    unsigned long long m = lanes(L.mode == M_IDLE);
+    cur = uniform(cur);
+    end = uniform(end);
+    drained = uniform(drained);
     while (m != 0ull) {
       if (cur >= end) {
-        if (drained >> seg & 1u) break;
+        if (hold || (drained >> seg & 1u)) break;
         unsigned int base = 0;
-        if (__lane_id() == 0) base = atomicAdd(T.ctr + C_FETCH(seg), FETCH_CHUNK);
-        base = __shfl(base, 0);
+        if (__lane_id() == 0) base = atomicAdd(cold_args()->T.ctr + C_FETCH(seg), FETCH_CHUNK);
+        base = dyn + uniform(base);
         if (base + FETCH_CHUNK >= len) drained |= 1u << seg;
         cur = off + min(base, len);
         end = off + min(base + FETCH_CHUNK, len);
         continue;
       }
       const unsigned int idx = cur + (unsigned int)__popcll(m & lanemask_lt());
-      if (slot < 0 && idx < end) {
+      if (L.mode == M_IDLE && idx < end) {
+        const TransitArgs *cold = cold_args();
+        const CloakP c = cold->c;
+        const Table T = cold->T;
         slot = T.order[idx];
         load_state(T, slot, L.x, L.v);
         L.t = 0.0;
-        L.h = o.h0;
+        L.h = cold->o.h0;
         L.ns = 0;
         L.bounces = 0;
         L.after_reject = false;
-        L.rid = -1;
+        L.mode = M_STEP;
         if constexpr (HAM) ham_convert<KIND>(c.a, c.kappa, L.x, L.v, true);  // v -> k
-        else accel<KIND>(c.a, L.x[0], L.x[1], L.v[0], L.v[1], L.v[2], L.A1[0], L.A1[1], L.A1[2]);
+        else if constexpr (SCH == RT_SCHEME_DP45)
+          accel<KIND>(c.a, L.x[0], L.x[1], L.v[0], L.v[1], L.v[2], L.A1[0], L.A1[1], L.A1[2]);
         if constexpr (FRES) L.wt = T.wt[slot];
       }
       cur = min(cur + (unsigned int)__popcll(m), end);
-      m = __ballot(slot < 0);
+      m = lanes(L.mode == M_IDLE);
     }
-    if (__ballot(slot >= 0) == 0ull) return;
+    if (!any_lane(L.mode < M_IDLE)) return;
 
     // A wave that holds a ray past LONG_RAY_ATTEMPTS attempts is on the
     // launch's critical path (the longest rays take ~1500 attempts where the
     // mean is ~40): give it issue priority over the waves that share its
     // SIMD, which fill the remaining issue slots.
-    if (__ballot(slot >= 0 && L.ns > LONG_RAY_ATTEMPTS) != 0ull) __builtin_amdgcn_s_setprio(3);
+    if (any_lane(L.mode < M_IDLE && L.ns > LONG_RAY_ATTEMPTS)) __builtin_amdgcn_s_setprio(3);
     else __builtin_amdgcn_s_setprio(0);
 
-    for (int it = 0; it < refill; ++it) {
-      if (slot >= 0) {
+    // nothing left to claim: look for a refill (and the priority) less often
+    const int period = (int)uniform((cur >= end && (hold || (drained >> seg & 1u))) ? DRAIN_PERIOD : refill);
+    for (int it = 0; it < period;) {
+      const bool go = L.mode < M_AT;
+      const unsigned long long going = lanes(go);
+      int done = 0;
+      if (go || __popcll(going) < FEW_LANES) done = advance<KIND, SCH>(L, go, hot, hoto, max_ns, tol, period - it);
+      // (equal in all lanes that took part)
+      it += going ? __builtin_amdgcn_readlane(done, __builtin_ctzll(going)) : period;
+      const unsigned long long wait = lanes(L.mode >= M_AT && L.mode < M_IDLE);
+      if (wait == 0ull) continue;
+      if (it < period && EVENT_SHARE * __popcll(wait) < __popcll(lanes(L.mode < M_IDLE))) continue;
+      if (L.mode >= M_AT && L.mode < M_IDLE) {
+        const TransitArgs *cold = cold_args();
+        const CloakP c = cold->c;
+        const OptsP o = cold->o;
+        const Table T = cold->T;
         double hr = __builtin_nan("");
-        const int stop = iterate<KIND, HAM, FRES>(L, c, o, tol, hr);
+        const int rid = L.mode - M_AT;
+        const int stop = L.mode < M_STOP ? interface_event<KIND, SCH, FRES>(L, c, o, max_ns, hr) : L.mode - M_STOP;
         if (stop >= 0) {
           // the Hamiltonian form holds k until an interface: report v
           if constexpr (HAM)
@@ -740,52 +871,127 @@ __device__ __forceinline__ void run_segment(const CloakP &c, const OptsP &o, con
           T.t[slot] = L.t;
           T.nsteps[slot] = L.ns;
           // bits 8..: the boundary an exited ray left through
-          T.bounces[slot] = L.bounces | (stop == RT_RAY_EXITED ? L.rid << 8 : 0);
+          T.bounces[slot] = L.bounces | (stop == RT_RAY_EXITED ? rid << 8 : 0);
           T.status[slot] = stop;
           T.hres[slot] = hr;
           if constexpr (FRES) T.wt[slot] = L.wt;
-          slot = -1;
+          L.mode = M_IDLE;
         }
       }
+      const int idle = __popcll(lanes(L.mode == M_IDLE));
+      if (idle == 64 || (idle >= IDLE_LANES && period == refill)) break;
     }
   }
 }
 
-template <bool HAM, bool FRES>
-__global__ void __launch_bounds__(256) k_transit(CloakP c, OptsP o, Table T, int refill) {
+// waves of a segment's part `share` of the first round that keep their SIMDs
+// to themselves (see k_transit): none where the part holds all `len` rays
+__device__ __forceinline__ unsigned int held_waves(unsigned int len, unsigned int share) {
+  return len > share * FETCH_CHUNK ? share / HOLD_SHARE : 0u;
+}
+
+template <int SCH, bool FRES>
+__global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FRES ? 1 : 4))) k_transit(TransitArgs G) {
   // the queue holds the used parts of the segments one after the other,
   // each sorted hardest first and holding one branch (every entry kernel
   // fills segment q with one (cloak, branch) pair); a wave integrates one
   // segment at a time and moves on to the next one that still has rays
-  const SegMap sm = seg_map(T);
-  const double tol = 1e-13 * c.b;
+  const SegMap sm = seg_map(G.T);
+  const double tol = 1e-13 * G.c.b;
   unsigned int drained = 0;  // bit q: this wave found segment q's queue exhausted
+  int kind[NSEG];
+  unsigned long long cost[NSEG], total = 0;
   int nused = 0;
 #pragma unroll
   for (int q = 0; q < NSEG; ++q) {
-    if (sm.off[q + 1] == sm.off[q]) drained |= 1u << q;
-    else ++nused;
+    kind[q] = K_RO;
+    cost[q] = 0;
+    if (sm.off[q + 1] == sm.off[q]) {
+      drained |= 1u << q;
+    } else {
+      ++nused;
+      kind[q] = (int)uniform(G.T.kind[(long long)q * G.T.cap]);
+      // a ray's usual cost by branch: radial-o, radial-e, azimuthal-o,
+      // azimuthal-e (DP45 attempts x instructions, ratios as measured over
+      // the 3-D render: 16, 31, 30 and 73 attempts)
+      const unsigned int w = kind[q] == K_RO ? 1 : (kind[q] == K_AE ? 15 : 7);
+      cost[q] = (unsigned long long)(sm.off[q + 1] - sm.off[q]) * w;
+      total += cost[q];
+    }
   }
   if (nused == 0) return;
-  // start on the (wave mod nused)-th used segment
-  const unsigned int wave = (blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  int seg = 0;
-  {
-    int k = (int)(wave % (unsigned int)nused);
-    for (int q = 0; q < NSEG; ++q)
-      if (!(drained >> q & 1u)) {
-        if (k == 0) { seg = q; break; }
-        --k;
-      }
+  // Each wave's first rays are fixed by its number, not raced for. The
+  // dispatcher fills the chip breadth first, so waves 0 .. simds-1 sit on
+  // SIMDs of their own, and so does every later round of that many. A round is
+  // shared out over the segments by their expected cost, so that they run dry
+  // at about the same time (a wave that changes segments first waits for its
+  // longest ray, its other lanes idle), segment q taking lanes n1[q] of it.
+  // Where a segment's part of the first round holds all of its rays, they are
+  // dealt out evenly over it, one ray per wave for the smallest calls, and
+  // the later rounds stay out; raced for, several of the waves that share a
+  // SIMD could win a chunk while other SIMDs idle.
+  // The hardest rays of a large segment, one wave in HOLD_SHARE of its first
+  // round, stay alone: their SIMDs' other waves leave, and their waves do not
+  // refill lanes while one of those rays is under way (a lane-mate's crossings
+  // and interfaces cost the wave ~30% more instructions per attempt, and the
+  // SIMD-mates' instructions delay its own). Such a ray's path next to r = a
+  // takes up to tens of thousands of attempts, which set the launch's length.
+  const unsigned int wave = uniform((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
+  const unsigned int nwave = gridDim.x * blockDim.x >> 6;
+  const unsigned int round = min(nwave, (unsigned int)G.simds), rounds = nwave / round;
+  const unsigned int at = wave % round;
+  unsigned int n1[NSEG], rank = ~0u, first = 0;  // rank: this wave's number within its segment (segment: seg)
+  int seg = 0, left = nused;
+#pragma unroll
+  for (int q = 0; q < NSEG; ++q) {
+    n1[q] = 0;
+    if (drained >> q & 1u) continue;
+    --left;
+    n1[q] = left ? 1u + (unsigned int)((round - nused) * cost[q] / total) : round - first;
+    if (at >= first && at < first + n1[q]) {
+      seg = q;
+      const unsigned int turn = wave / round, pos = at - first;
+      const unsigned int held = held_waves(sm.off[q + 1] - sm.off[q], n1[q]);
+      if (turn > 0 && pos < held) return;
+      if (turn < rounds) rank = turn == 0 ? pos : n1[q] + (turn - 1) * (n1[q] - held) + (pos - held);
+    }
+    first += n1[q];
   }
-  while (drained != (1u << NSEG) - 1u) {
+  for (;;) {
+    drained = uniform(drained);
+    if (drained == (1u << NSEG) - 1u) break;
     while (drained >> seg & 1u) seg = (seg + 1) % NSEG;
-    const int kind = __builtin_amdgcn_readfirstlane(T.kind[(long long)seg * T.cap]);
-    switch (kind) {
-      case K_RE: run_segment<K_RE, HAM, FRES>(c, o, T, sm, seg, tol, refill, drained); break;
-      case K_AO: run_segment<K_AO, HAM, FRES>(c, o, T, sm, seg, tol, refill, drained); break;
-      case K_AE: run_segment<K_AE, HAM, FRES>(c, o, T, sm, seg, tol, refill, drained); break;
-      default: run_segment<K_RO, HAM, FRES>(c, o, T, sm, seg, tol, refill, drained); break;
+    unsigned int off = 0, len = 0, share = 0;
+    int k = K_RO;
+#pragma unroll
+    for (int q = 0; q < NSEG; ++q)
+      if (q == seg) {
+        off = sm.off[q];
+        len = sm.off[q + 1] - off;
+        share = n1[q];
+        k = kind[q];
+      }
+    const bool small = len <= share * FETCH_CHUNK;
+    const unsigned int held = held_waves(len, share);
+    const unsigned int nst = small ? share : share + (rounds - 1) * (share - held);  // waves with rays of their own
+    const unsigned int c0 = small ? (len + share - 1) / share : FETCH_CHUNK;  // rays each
+    const unsigned int dyn = min(nst * c0, len);
+    unsigned int cur = 0, end = 0;
+    if (rank < nst) {
+      cur = min(rank * c0, len);
+      end = min(cur + c0, len);
+    }
+    const bool hold = rank < held;
+    rank = ~0u;
+    if (dyn >= len) drained |= 1u << seg;
+    if (end <= cur && dyn >= len) continue;
+    cur += off;
+    end += off;
+    switch (k) {
+      case K_RE: run_segment<K_RE, SCH, FRES>(G.c, G.o, seg, off, len, tol, G.refill, cur, end, dyn, hold, drained); break;
+      case K_AO: run_segment<K_AO, SCH, FRES>(G.c, G.o, seg, off, len, tol, G.refill, cur, end, dyn, hold, drained); break;
+      case K_AE: run_segment<K_AE, SCH, FRES>(G.c, G.o, seg, off, len, tol, G.refill, cur, end, dyn, hold, drained); break;
+      default: run_segment<K_RO, SCH, FRES>(G.c, G.o, seg, off, len, tol, G.refill, cur, end, dyn, hold, drained); break;
     }
   }
 }
@@ -1870,20 +2076,25 @@ unsigned int grid_for(long long n, int block) {
   return (unsigned int)std::max(1LL, g);
 }
 
-template <bool HAM, bool FRES>
-unsigned int transit_grid_t(int block) {
-  int occ = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, k_transit<HAM, FRES>, block, 0) != hipSuccess || occ <= 0)
-    occ = 1;
-  return (unsigned int)(num_cu() * occ);
+// the integrator variant the options select: a scheme, with or without the
+// Eq. (12) weights
+using TransitKernel = void (*)(TransitArgs);
+TransitKernel transit_kernel(const OptsP &o, bool fres) {
+  switch (o.scheme) {
+    case RT_SCHEME_RK4: return fres ? k_transit<RT_SCHEME_RK4, true> : k_transit<RT_SCHEME_RK4, false>;
+    case RT_SCHEME_RK4_HAM: return fres ? k_transit<RT_SCHEME_RK4_HAM, true> : k_transit<RT_SCHEME_RK4_HAM, false>;
+    case RT_SCHEME_RK4_HAMC:
+      return fres ? k_transit<RT_SCHEME_RK4_HAMC, true> : k_transit<RT_SCHEME_RK4_HAMC, false>;
+    default: return fres ? k_transit<RT_SCHEME_DP45, true> : k_transit<RT_SCHEME_DP45, false>;
+  }
 }
 
-// the integrator variant the options select: Eq. (8) in (x, v) or the
-// Hamiltonian form, with or without the Eq. (12) weights
+// blocks of `block` threads that the chip holds at once
 unsigned int transit_grid(const OptsP &o, int block, bool fres = false) {
-  if (o.scheme == RT_SCHEME_RK4_HAM || o.scheme == RT_SCHEME_RK4_HAMC)
-    return fres ? transit_grid_t<true, true>(block) : transit_grid_t<true, false>(block);
-  return fres ? transit_grid_t<false, true>(block) : transit_grid_t<false, false>(block);
+  int occ = 0;
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&occ, transit_kernel(o, fres), block, 0) != hipSuccess || occ <= 0)
+    occ = 1;
+  return (unsigned int)(num_cu() * occ);
 }
 
 // integrate the slots already placed in the table: order them hardest
@@ -1896,15 +2107,8 @@ void run_transit(const CloakP &c, const OptsP &o, const Table &T, int block, int
   ProfEvent pe;
   bool on = false;
   if (profile) prof_begin(s, pe, on);
-  const bool ham = o.scheme == RT_SCHEME_RK4_HAM || o.scheme == RT_SCHEME_RK4_HAMC;
-  if (ham && fres)
-    hipLaunchKernelGGL((k_transit<true, true>), dim3(grid), dim3(block), 0, s, c, o, T, refill);
-  else if (ham)
-    hipLaunchKernelGGL((k_transit<true, false>), dim3(grid), dim3(block), 0, s, c, o, T, refill);
-  else if (fres)
-    hipLaunchKernelGGL((k_transit<false, true>), dim3(grid), dim3(block), 0, s, c, o, T, refill);
-  else
-    hipLaunchKernelGGL((k_transit<false, false>), dim3(grid), dim3(block), 0, s, c, o, T, refill);
+  hipLaunchKernelGGL(transit_kernel(o, fres), dim3(grid), dim3(block), 0, s,
+                     TransitArgs{c, o, T, refill, 4 * num_cu()});
   if (profile) prof_end(s, pe, on);
 }
 
@@ -1930,7 +2134,7 @@ struct RenderJob {
   std::vector<CamP> cams;
   float table[64] = {0};
   long long total = 0, chunk = 0, npix = 0;
-  int n_cloaks = 0, block = 256, refill = 2;
+  int n_cloaks = 0, block = 256, refill = DEFAULT_REFILL;
   unsigned int grid = 0;
   TuneKey key{};
 };
@@ -2033,7 +2237,7 @@ int prepare_render(const rt_cloak *cloaks, int32_t n_cloaks, const rt_trace_opts
   J.n_cloaks = n_cloaks;
   J.key = TuneKey{n_cloaks, n_cams, w, h, spp, pol_mask, opts->scheme, opts->precision};
   J.block = opts->block ? opts->block : 256;
-  J.refill = opts->refill_period ? opts->refill_period : 2;
+  J.refill = opts->refill_period ? opts->refill_period : DEFAULT_REFILL;
   if (!opts->block && !opts->refill_period) {
     std::lock_guard<std::mutex> lk(g_tune_mu);
     auto it = g_tuned.find(J.key);
@@ -2494,7 +2698,7 @@ int enqueue_trace(rt_cloak cloak, const rt_trace_opts *opts, int32_t pol, int64_
   CloakP c = make_cloak(cloak->d);
   OptsP o = make_opts(*opts);
   int block = opts->block ? opts->block : 256;
-  int refill = opts->refill_period ? opts->refill_period : 2;
+  int refill = opts->refill_period ? opts->refill_period : DEFAULT_REFILL;
   int kind = c.axis * 2 + pol;
   const bool fres = trans != nullptr;
   unsigned int grid = transit_grid(o, block, fres);
@@ -2545,7 +2749,7 @@ int rt_transit_exact(const rt_cloak *cloaks, int32_t n_cloaks, const rt_trace_op
   CloakP c = make_cloak(cloaks[0]->d);
   OptsP o = make_opts(*opts);
   int block = opts->block ? opts->block : 256;
-  int refill = opts->refill_period ? opts->refill_period : 2;
+  int refill = opts->refill_period ? opts->refill_period : DEFAULT_REFILL;
   unsigned int grid = transit_grid(o, block);
   hipLaunchKernelGGL(k_zero, dim3((C_COUNT + 255) / 256), dim3(256), 0, s, T.ctr, (int)C_COUNT);
   hipLaunchKernelGGL(k_sx_entry, dim3(grid_for(n, 256)), dim3(256), 0, s, c, o, T, (long long)n,
