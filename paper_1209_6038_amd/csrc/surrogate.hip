@@ -55,9 +55,9 @@ constexpr long long OFF_W5 = OFF_B4 + HID;
 constexpr long long OFF_B5 = OFF_W5 + HID * NOUT;
 constexpr long long NPARAM = OFF_B5 + NOUT;  // 200,453
 static_assert(OFF_B1 == OFF_W1 + NIN * HID, "W1, b1 are contiguous");
-// BF16 copies of W2, W3, W4: transposed [out][in] (forward: the 8
-// consecutive inputs an MFMA lane needs for one output are one 16-byte
-// load) and row-major [in][out] (backward through the layer); NBF per copy
+// BF16 copies of W2, W3, W4, twice in MFMA operand order (frag_index): with
+// the outputs as units (forward), then with the inputs as units (backward
+// through the layer); NBF per copy
 constexpr long long NBF = 3LL * HID * HID;
 // scaling block: in_off[6], in_scale[6], out_mean[5], out_std[5], then the loss
 constexpr int S_INOFF = 0, S_INSCALE = 6, S_OMEAN = 12, S_OSTD = 17, S_LOSS = 22, NSCAL = 24;
@@ -97,311 +97,6 @@ __device__ __forceinline__ float silu_f(float z) { return z * sigmoid_f(z); }
 __device__ __forceinline__ float dsilu_f(float z) {
   const float s = sigmoid_f(z);
   return s * (1.0f + z * (1.0f - s));
-}
-
-// ---------------------------------------------------------------------------
-// Tiled GEMM on MFMA: C(M x N) = A(M x K) B(K x N) with both operands
-// contiguous along K (A(i,k) = A[i*lda + k], B(k,j) = B[j*ldb + k]), BF16 in, FP32
-// accumulation. 64 x 64 tile per 256-thread block (4 waves of 32 x 32, each
-// 2 x 2 MFMA 16x16x32 tiles), K in steps of 32 staged through LDS, optionally
-// split over K (each split covers `kchunk` of K). One-dimensional grid of
-// (column tiles) x (row tiles) x (splits) blocks, the column tile fastest.
-// Consecutive blocks go to the 8 XCDs in turn, each with its own L2, so the
-// block number is first renumbered to give each XCD a contiguous range of
-// tiles: the column tiles of a row tile (which read the same A rows), and the
-// tiles of a K split (which read the same A and B columns), then share an L2.
-// Epilogues (the backward pass of the BF16 layers):
-//   EPI_DSILU      g = acc * silu'(Z): Cf <- g, Cb <- bf16(g), its
-//                  transpose Cbt <- bf16(g)^T ([N][ldcbt]), and the
-//                  block's column sums of g to the row of colsum of its
-//                  row tile (a partial-sum array [row tiles][N], may be NULL;
-//                  with xf, [row tiles][7][N] holding xf^T g, then the sums:
-//                  the gradients of W1 and b1 when g is dz of layer 1)
-//   EPI_SPLIT      Cf + split * M * ldcf <- acc: one partial product per K
-//                  split, summed afterwards by k_sum_rows
-// (each output pointer may be NULL)
-// ---------------------------------------------------------------------------
-enum { EPI_DSILU = 1, EPI_SPLIT = 2 };
-
-struct Gemm {
-  const bf16 *A;
-  long long lda;  // A(i, k) = A[i * lda + k]
-  const bf16 *B;
-  long long ldb;  // B(k, j) = B[j * ldb + k]
-  bool veca, vecb;  // 16-byte operand loads allowed
-  int M, N, K, kchunk, epi;
-  int nct, nrt;  // column and row tiles
-  const float *Z;
-  long long ldz;
-  float *Cf;
-  long long ldcf;
-  bf16 *Cb;
-  long long ldcb;
-  float *colsum;  // EPI_DSILU: per-block column sums of g, [row tile][N] (may be NULL)
-  const float *xf;  // with colsum: the layer-1 inputs [M][6], for the sums xf^T g ([row tile][7][N])
-  bf16 *Cbt;      // EPI_DSILU: bf16(g) transposed, Cbt[col * ldcbt + row] (may be NULL)
-  long long ldcbt;
-};
-
-// Operand tiles are staged 64 deep in K: a 64 x 64 BF16 tile (rows r0..,
-// k k0..) is two 16-byte vectors per thread, 8 consecutive threads on the 128
-// bytes of one row. P(row, k) = P[row * ld + k] (K contiguous); rows < nrow
-// and k < kend valid, zeros elsewhere (vec: ld and P allow 16-byte loads).
-constexpr int GT = 64, GK = 64, GLD = GK + 8;  // tile, K step, padded LDS row
-
-__device__ __forceinline__ void load_op(bf16x8 v[2], const bf16 *__restrict__ P, long long ld, bool vec, int r0,
-                                        int nrow, int k0, int kend, int tid) {
-#pragma unroll
-  for (int p = 0; p < 2; ++p) {
-    const int gr = r0 + (tid >> 3) + 32 * p, gk = k0 + 8 * (tid & 7);
-    const bf16 *src = P + (long long)gr * ld + gk;
-    if (vec && gr < nrow && gk + 8 <= kend) {
-      v[p] = *reinterpret_cast<const bf16x8 *>(src);
-    } else {
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[p][e] = (gr < nrow && gk + e < kend) ? src[e] : (bf16)0.0f;
-    }
-  }
-}
-
-__device__ __forceinline__ void store_op(bf16 *T, const bf16x8 v[2], int tid) {
-#pragma unroll
-  for (int p = 0; p < 2; ++p) *reinterpret_cast<bf16x8 *>(&T[((tid >> 3) + 32 * p) * GLD + 8 * (tid & 7)]) = v[p];
-}
-
-// C = A B over the block's K range with an epilogue: a 64 x 64 tile, 4 waves
-// in 2 x 2, each owning 32 x 32 outputs as 2 x 2 MFMA 16x16x32 tiles. The K
-// loop is double-buffered: step i's tiles go from registers to one LDS stage
-// while step i + 1's global loads are in flight, so one barrier per 64-deep
-// step; the epilogue's inputs (the pre-activations) are loaded before the
-// loop. The FP32 output tile reuses the staging area.
-__global__ void __launch_bounds__(256) k_gemm(Gemm g) {
-  constexpr int BM = GT, BN = GT, WM = 2, WN = 2, STAGE = (BM + BN) * GLD;
-  __shared__ __attribute__((aligned(16))) bf16 sm[2 * STAGE];
-  static_assert(BM * (BN + 4) * sizeof(float) <= sizeof(sm), "the FP32 tile fits in the staging area");
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const int wm = w >> 1, wn = w & 1;
-  const unsigned nb = gridDim.x, b = blockIdx.x;
-  const unsigned t = (nb & 7) ? b : (b & 7) * (nb >> 3) + (b >> 3);  // a bijection of [0, nb)
-  const int ct = (int)(t % (unsigned)g.nct), rt = (int)(t / (unsigned)g.nct % (unsigned)g.nrt);
-  const int split = (int)(t / (unsigned)g.nct / (unsigned)g.nrt);
-  const int row0 = rt * BM, col0 = ct * BN;
-  const int kbeg = split * g.kchunk, kend = min(g.K, kbeg + g.kchunk);
-  // this thread's 16 epilogue entries: row lr, columns lc.. of the tile
-  const int lr = tid >> 2, lc = (tid & 3) * 16;
-  float zp[16];
-  const bool zpre = g.epi == EPI_DSILU && row0 + lr < g.M && col0 + lc + 16 <= g.N;
-  if (zpre) {
-    const float *zr = g.Z + (long long)(row0 + lr) * g.ldz + col0 + lc;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4 zz = *reinterpret_cast<const float4 *>(zr + 4 * q);
-      zp[4 * q] = zz.x; zp[4 * q + 1] = zz.y; zp[4 * q + 2] = zz.z; zp[4 * q + 3] = zz.w;
-    }
-  }
-  f32x4 acc[WM][WN];
-#pragma unroll
-  for (int i = 0; i < WM; ++i)
-#pragma unroll
-    for (int j = 0; j < WN; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
-  // A(i, k) = A[i*lda + k]; B staged as its transpose, B(k, j) = B[j*ldb + k]
-  bf16x8 ra[2], rb[2];
-  load_op(ra, g.A, g.lda, g.veca, row0, g.M, kbeg, kend, tid);
-  load_op(rb, g.B, g.ldb, g.vecb, col0, g.N, kbeg, kend, tid);
-  const int nk = (kend - kbeg + GK - 1) / GK;
-  for (int it = 0; it < nk; ++it) {
-    bf16 *As = sm + (it & 1) * STAGE, *Bs = As + BM * GLD;
-    store_op(As, ra, tid);
-    store_op(Bs, rb, tid);
-    __syncthreads();  // also: every wave is done with this stage's previous use (step it - 2)
-    if (it + 1 < nk) {
-      const int k1 = kbeg + (it + 1) * GK;
-      load_op(ra, g.A, g.lda, g.veca, row0, g.M, k1, kend, tid);
-      load_op(rb, g.B, g.ldb, g.vecb, col0, g.N, k1, kend, tid);
-    }
-    // operand layout of v_mfma_f32_16x16x32_bf16: lane l holds
-    // A[l%16][8*(l/16) + j] and B[8*(l/16) + j][l%16], j = 0..7 (padded rows
-    // of 144 bytes keep each 8-element read 16-byte aligned and spread the
-    // 16 rows of a read over all banks)
-#pragma unroll
-    for (int ks = 0; ks < GK; ks += 32) {
-      bf16x8 af[WM], bfr[WN];
-#pragma unroll
-      for (int i = 0; i < WM; ++i)
-        af[i] = *reinterpret_cast<const bf16x8 *>(&As[(wm * 32 + i * 16 + (lane & 15)) * GLD + ks + 8 * (lane >> 4)]);
-#pragma unroll
-      for (int j = 0; j < WN; ++j)
-        bfr[j] = *reinterpret_cast<const bf16x8 *>(&Bs[(wn * 32 + j * 16 + (lane & 15)) * GLD + ks + 8 * (lane >> 4)]);
-#pragma unroll
-      for (int i = 0; i < WM; ++i)
-#pragma unroll
-        for (int j = 0; j < WN; ++j)
-          acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bfr[j], acc[i][j], 0, 0, 0);
-    }
-  }
-  __syncthreads();  // every wave has read its last operands: the staging area becomes the FP32 tile
-  // result layout: lane l holds D[4*(l/16) + i][l%16], i = 0..3
-  // the elementwise epilogues read and write whole rows: the tile goes
-  // through LDS, and each thread then owns 16 consecutive columns of a row
-  // (64-byte FP32 and 32-byte BF16 vectors, full cache lines per row)
-  float(*Cs)[BN + 4] = reinterpret_cast<float(*)[BN + 4]>(sm);
-  // beyond the FP32 tile: the layer-1 inputs of the tile's rows [64][6] and
-  // the column sums of the 4 waves [4][7][64]
-  float *const xs = &Cs[BM][0];
-  float *const red = xs + BM * NIN;
-  static_assert((BM * (BN + 4) + BM * NIN + 4 * (NIN + 1) * 64) * sizeof(float) <= sizeof(sm), "epilogue LDS");
-  if (g.epi == EPI_DSILU && g.colsum && g.xf)
-    for (int e = tid; e < BM * NIN; e += 256) {
-      const int r = e / NIN;
-      xs[e] = row0 + r < g.M ? g.xf[(long long)(row0 + r) * NIN + e % NIN] : 0.0f;
-    }
-#pragma unroll
-  for (int ti = 0; ti < WM; ++ti)
-#pragma unroll
-    for (int tj = 0; tj < WN; ++tj)
-#pragma unroll
-      for (int r = 0; r < 4; ++r)
-        Cs[wm * 16 * WM + ti * 16 + 4 * (lane >> 4) + r][wn * 16 * WN + tj * 16 + (lane & 15)] = acc[ti][tj][r];
-  __syncthreads();
-  static_assert(BM == 64 && BN == 64, "one epilogue pass: 16 entries per thread");
-  do {
-    const int row = row0 + lr, col = col0 + lc;
-    const bool sums = g.epi == EPI_DSILU && (g.colsum || g.Cbt);  // g stays in the tile
-    if (row >= g.M) {
-      if (sums) {
-#pragma unroll
-        for (int e = 0; e < 16; ++e) Cs[lr][lc + e] = 0.0f;
-      }
-      break;
-    }
-    float v[16];
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      const float4 t = *reinterpret_cast<const float4 *>(&Cs[lr][lc + 4 * q]);
-      v[4 * q] = t.x; v[4 * q + 1] = t.y; v[4 * q + 2] = t.z; v[4 * q + 3] = t.w;
-    }
-    if (g.epi == EPI_SPLIT) {
-      float *o = g.Cf + (long long)split * g.M * g.ldcf + (long long)row * g.ldcf + col;
-      if (col + 16 <= g.N) {
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<float4 *>(o + 4 * q) = float4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-      } else {
-        for (int e = 0; e < 16 && col + e < g.N; ++e) o[e] = v[e];
-      }
-      break;
-    }
-    if (col + 16 <= g.N) {
-#pragma unroll
-      for (int e = 0; e < 16; ++e) v[e] *= dsilu_f(zp[e]);  // zpre holds here
-      if (g.Cf) {
-        float *o = g.Cf + (long long)row * g.ldcf + col;
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<float4 *>(o + 4 * q) = float4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-      }
-      if (g.Cb) {
-        bf16x8 b0, b1;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { b0[e] = (bf16)v[e]; b1[e] = (bf16)v[8 + e]; }
-        bf16 *o = g.Cb + (long long)row * g.ldcb + col;
-        *reinterpret_cast<bf16x8 *>(o) = b0;
-        *reinterpret_cast<bf16x8 *>(o + 8) = b1;
-      }
-      if (sums) {
-        // this thread's own 16 entries of the staged tile, now holding g
-#pragma unroll
-        for (int q = 0; q < 4; ++q)
-          *reinterpret_cast<float4 *>(&Cs[lr][lc + 4 * q]) = float4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
-      }
-    } else {
-      for (int e = 0; e < 16; ++e) {
-        const long long c = col + e;
-        const float d = c < g.N ? v[e] * dsilu_f(g.Z[row * g.ldz + c]) : 0.0f;
-        if (sums) Cs[lr][lc + e] = d;
-        if (c >= g.N) continue;
-        if (g.Cf) g.Cf[row * g.ldcf + c] = d;
-        if (g.Cb) g.Cb[row * g.ldcb + c] = (bf16)d;
-      }
-    }
-  } while (false);
-  if (g.epi == EPI_DSILU && (g.colsum || g.Cbt)) __syncthreads();
-  if (g.epi == EPI_DSILU && g.Cbt) {
-    // every thread has left g (zeros outside the matrix) in its entries of
-    // the staged tile: the transpose, 8 consecutive rows of one column per
-    // 16-byte store
-    // (BM / 8 consecutive threads on the consecutive pieces of one column)
-    static_assert(BM % 8 == 0 && (BM / 8) * BN % 256 == 0, "transposed pieces per thread");
-    for (int e = tid; e < (BM / 8) * BN; e += 256) {
-      const int c = e / (BM / 8), r8 = (e % (BM / 8)) * 8;
-      const int col = col0 + c, row = row0 + r8;
-      if (col >= g.N || row >= g.M) continue;
-      bf16 *o = g.Cbt + (long long)col * g.ldcbt + row;
-      if (row + 8 <= g.M) {
-        bf16x8 pk;
-#pragma unroll
-        for (int k = 0; k < 8; ++k) pk[k] = (bf16)Cs[r8 + k][c];
-        *reinterpret_cast<bf16x8 *>(o) = pk;
-      } else {
-        for (int k = 0; row + k < g.M; ++k) o[k] = (bf16)Cs[r8 + k][c];
-      }
-    }
-  }
-  if (g.epi == EPI_DSILU && g.colsum) {
-    // the tile's column sums of g and, with xf, before them the sums of
-    // xf[row][k] g[row][col], k < 6: one row of partial sums per row tile,
-    // [row tile][7][N] (or [row tile][N]), added up by k_sum_rows (no
-    // atomics). Wave w sums rows 16 w .. 16 w + 15 for column `lane`, then
-    // the 4 waves' sums are added through LDS.
-    static_assert(BN == 64, "one column per lane");
-    constexpr int NS = NIN + 1;
-    float sk[NS];
-#pragma unroll
-    for (int k = 0; k < NS; ++k) sk[k] = 0.0f;
-#pragma unroll 4
-    for (int r = 16 * w; r < 16 * w + 16; ++r) {
-      const float gv = Cs[r][lane];
-      sk[NIN] += gv;
-      if (g.xf) {
-#pragma unroll
-        for (int k = 0; k < NIN; ++k) sk[k] = fmaf(xs[r * NIN + k], gv, sk[k]);
-      }
-    }
-#pragma unroll
-    for (int k = 0; k < NS; ++k) red[(w * NS + k) * 64 + lane] = sk[k];
-    __syncthreads();
-    const int nsum = g.xf ? NS : 1;
-    for (int e = tid; e < nsum * BN; e += 256) {
-      const int k = e / BN, c = e % BN, src = g.xf ? k : NIN;
-      const float v = (red[src * 64 + c] + red[(NS + src) * 64 + c]) +
-                      (red[(2 * NS + src) * 64 + c] + red[(3 * NS + src) * 64 + c]);
-      if (col0 + c < g.N) g.colsum[((long long)rt * nsum + k) * g.N + col0 + c] = v;
-    }
-  }
-}
-
-// dst[c] += sum over r < rows of part[r * ld + c], c < ncols. Block (x, y):
-// 64 consecutive columns x 4 groups of rows y*4+q, y*4+q+4Y, ... (Y =
-// gridDim.y) summed in registers, then over the 4 groups in LDS, one atomic
-// per column and block row (gridDim.y = 1: a single writer per column).
-__global__ void __launch_bounds__(256) k_sum_rows(const float *__restrict__ part, int rows, long long ld,
-                                                  int ncols, float *__restrict__ dst) {
-  __shared__ float sh[4][64];
-  const int c = threadIdx.x & 63, q = threadIdx.x >> 6;
-  const long long col = (long long)blockIdx.x * 64 + c;
-  float s0 = 0.f, s1 = 0.f;
-  if (col < ncols) {
-    const int step = 4 * gridDim.y;
-    int r = blockIdx.y * 4 + q;
-    for (; r + step < rows; r += 2 * step) {
-      s0 += part[(long long)r * ld + col];
-      s1 += part[(long long)(r + step) * ld + col];
-    }
-    if (r < rows) s0 += part[(long long)r * ld + col];
-  }
-  sh[q][c] = s0 + s1;
-  __syncthreads();
-  if (q == 0 && col < ncols) atomicAdd(&dst[col], (sh[0][c] + sh[1][c]) + (sh[2][c] + sh[3][c]));
 }
 
 // ---------------------------------------------------------------------------
@@ -636,128 +331,6 @@ __global__ void k_destd(const float *__restrict__ y, int n, long long ld, const 
   t[o * ld + row] = fmaf(y[i], sc[S_OSTD + o], sc[S_OMEAN + o]);
 }
 
-// backward of layer 5 (FP32): dW5 = a4^T dy, db5 = sum dy, with a4 =
-// silu(z4) recomputed from the saved pre-activation (the same FP32 function
-// as the forward's), dz4 = (dy W5^T) * silu'(z4) -> BF16 for the next
-// product (row-major and transposed), and db4 = sum dz4 (FP32). A block
-// takes a run of rows in chunks of 64, wave w rows 16 w .. 16 w + 15 of a
-// chunk, lane l units 4 l .. 4 l + 3 (one 16-byte load per lane covers a
-// row's 256 units); the transposed copy goes through LDS and out in whole
-// 128-byte lines. Each block writes its partial sums of the 1,541 gradient
-// entries b4 [256], W5 [256][5], b5 [5] (contiguous in the parameter vector
-// from OFF_B4) to a row of `part`.
-constexpr int L5_N = HID + HID * NOUT + NOUT, L5_LD = 1544, L5_MAXB = 1024;
-static_assert(OFF_W5 == OFF_B4 + HID && OFF_B5 == OFF_W5 + HID * NOUT, "b4, W5, b5 are contiguous");
-
-__global__ void __launch_bounds__(256) k_layer5_back(const float *__restrict__ dy, const float *__restrict__ z4,
-                                                     int n, const float *__restrict__ P, float *__restrict__ part,
-                                                     bf16 *__restrict__ dzb, bf16 *__restrict__ dzT, long long ldT) {
-  // unit u's 8 pieces of 8 rows of a chunk at tp[9 u + p]; afterwards the
-  // same memory holds the 4 waves' partial sums
-  __shared__ bf16x8 tp[HID * 9];
-  const int tid = threadIdx.x, lane = tid & 63;
-  const int w = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int u0 = 4 * lane;
-  float w5[4][NOUT], gw[4][NOUT], gz[4] = {0.f, 0.f, 0.f, 0.f}, gb[NOUT];
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-#pragma unroll
-    for (int o = 0; o < NOUT; ++o) {
-      w5[i][o] = P[OFF_W5 + (u0 + i) * NOUT + o];
-      gw[i][o] = 0.0f;
-    }
-#pragma unroll
-  for (int o = 0; o < NOUT; ++o) gb[o] = 0.0f;
-  const int per = (((n + gridDim.x - 1) / gridDim.x) + 63) & ~63;
-  const int r0 = blockIdx.x * per, r1 = min(n, r0 + per);
-  for (int c0 = r0; c0 < r1; c0 += 64) {
-    const int c1 = min(r1, c0 + 64);
-#pragma unroll
-    for (int p = 0; p < 2; ++p) {
-      const int rb = c0 + 16 * w + 8 * p;
-      // the 8 rows' loads together (rows past the chunk repeat its last
-      // row and are not used)
-      float4 zz[8];
-      float d[8][NOUT];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const long long row = min(rb + k, c1 - 1);
-        zz[k] = *reinterpret_cast<const float4 *>(&z4[row * HID + u0]);
-#pragma unroll
-        for (int o = 0; o < NOUT; ++o) d[k][o] = dy[row * NOUT + o];
-      }
-      bf16x8 pk[4];
-#pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        const float zk[4] = {zz[k].x, zz[k].y, zz[k].z, zz[k].w};
-        bf16x4 out;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) {
-          const float a = silu_f(zk[i]);
-          float da = 0.f;
-#pragma unroll
-          for (int o = 0; o < NOUT; ++o) da = fmaf(d[k][o], w5[i][o], da);
-          const float g = da * dsilu_f(zk[i]);
-          out[i] = (bf16)g;
-          pk[i][k] = out[i];
-          if (rb + k < c1) {
-            gz[i] += g;
-#pragma unroll
-            for (int o = 0; o < NOUT; ++o) gw[i][o] = fmaf(a, d[k][o], gw[i][o]);
-          }
-        }
-        if (rb + k < c1) {
-#pragma unroll
-          for (int o = 0; o < NOUT; ++o) gb[o] += d[k][o];
-          *reinterpret_cast<bf16x4 *>(&dzb[(long long)(rb + k) * HID + u0]) = out;
-        }
-      }
-      if (rb < c1) {
-#pragma unroll
-        for (int i = 0; i < 4; ++i) tp[9 * (u0 + i) + ((rb - c0) >> 3)] = pk[i];
-      }
-    }
-    __syncthreads();
-    for (int e = tid; e < 8 * HID; e += 256) {
-      const int u = e >> 3, p = e & 7, row = c0 + 8 * p;
-      if (row >= c1) continue;
-      const bf16x8 v = tp[9 * u + p];
-      bf16 *o = dzT + (long long)u * ldT + row;
-      if (row + 8 <= c1) {
-        *reinterpret_cast<bf16x8 *>(o) = v;
-      } else {
-        for (int k = 0; row + k < c1; ++k) o[k] = v[k];
-      }
-    }
-    __syncthreads();
-  }
-  // the 4 waves' sums: [wave][unit][W5 row (5), b4], then db5 [wave][5]
-  float *red = reinterpret_cast<float *>(tp);
-  static_assert((4 * HID * (NOUT + 1) + 4 * NOUT) * sizeof(float) <= sizeof(tp), "reduction fits");
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-#pragma unroll
-    for (int o = 0; o < NOUT; ++o) red[(w * HID + u0 + i) * (NOUT + 1) + o] = gw[i][o];
-    red[(w * HID + u0 + i) * (NOUT + 1) + NOUT] = gz[i];
-  }
-  if (lane == 0) {
-#pragma unroll
-    for (int o = 0; o < NOUT; ++o) red[4 * HID * (NOUT + 1) + w * NOUT + o] = gb[o];
-  }
-  __syncthreads();
-  float *pb = part + (long long)blockIdx.x * L5_LD;
-  for (int e = tid; e < HID * (NOUT + 1); e += 256) {
-    const int u = e / (NOUT + 1), k = e % (NOUT + 1);
-    constexpr int WS = HID * (NOUT + 1);
-    const float v = (red[e] + red[WS + e]) + (red[2 * WS + e] + red[3 * WS + e]);
-    pb[k == NOUT ? u : HID + u * NOUT + k] = v;
-  }
-  if (tid < NOUT) {
-    const float *rb = red + 4 * HID * (NOUT + 1);
-    pb[HID + HID * NOUT + tid] = (rb[tid] + rb[NOUT + tid]) + (rb[2 * NOUT + tid] + rb[3 * NOUT + tid]);
-  }
-}
-
 __global__ void k_fill(float *p, long long n, float v) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -773,17 +346,27 @@ __device__ __forceinline__ bool is_bias(long long i) {
          (i >= OFF_B4 && i < OFF_W5) || i >= OFF_B5;
 }
 
-// index of FP32 parameter i in the transposed BF16 copy (-1: no copy);
-// its row-major copy sits at NBF + (layer offset + e)
-__device__ __forceinline__ long long bf16_index(long long i, long long &rowmajor) {
+// The BF16 weights of a hidden layer are kept in the order the matrix cores
+// take them: an operand fragment is 16 units x 32 consecutive k, lane (q, c16)
+// holding unit c16, k = 8 q..8 q + 7, and a fragment's 64 x 16 bytes are
+// contiguous, so that a wave's load of one is 8 full cache lines (as rows of
+// 256 k it touched half of 16).
+__host__ __device__ __forceinline__ constexpr int frag_index(int unit, int k) {
+  return ((unit >> 4) * (HID / 32) + (k >> 5)) * 512 + (16 * (k >> 3 & 3) + (unit & 15)) * 8 + (k & 7);
+}
+
+// index of FP32 parameter i in the BF16 copy whose units are the layer's
+// outputs (k its inputs: forward); -1: no copy. Its index in the copy with
+// units and k exchanged (backward) goes to back.
+__device__ __forceinline__ long long bf16_index(long long i, long long &back) {
   long long l, e;
   if (i >= OFF_W2 && i < OFF_B2) { l = 0; e = i - OFF_W2; }
   else if (i >= OFF_W3 && i < OFF_B3) { l = 1; e = i - OFF_W3; }
   else if (i >= OFF_W4 && i < OFF_B4) { l = 2; e = i - OFF_W4; }
   else return -1;
-  const long long in = e / HID, out = e - in * HID;
-  rowmajor = NBF + l * HID * HID + e;
-  return l * HID * HID + out * HID + in;
+  const int in = (int)(e / HID), out = (int)(e - in * HID);
+  back = NBF + l * HID * HID + frag_index(in, out);
+  return l * HID * HID + frag_index(out, in);
 }
 
 // AdamW (decoupled weight decay on the weights, not the biases) on the FP32
@@ -1164,7 +747,7 @@ __global__ void __launch_bounds__(256) k_gate_idx(const float *__restrict__ x6, 
 // an operand read touches fall in distinct banks). Each hidden layer is
 // computed transposed, out^T = W^T act^T, so that an MFMA 16x16x32 tile's
 // A operand is 8 consecutive inputs of one output unit (one 16-byte load of
-// the transposed BF16 weights, streamed from L2), its B operand 8
+// the BF16 weights in operand order, streamed from L2), its B operand 8
 // consecutive inputs of one row (one 16-byte LDS read), and each lane's 4
 // results are 4 consecutive output units of one row (one 8-byte LDS store).
 // Wave w owns output units 64w..64w+63: 4 unit tiles x 8 row tiles, 128 FP32
@@ -1174,53 +757,6 @@ __global__ void __launch_bounds__(256) k_gate_idx(const float *__restrict__ x6, 
 // writes the standardized outputs (n x 5).
 // ---------------------------------------------------------------------------
 constexpr int FR = 128, ALD = HID + 8;
-
-// copy the block's BF16 activation tile (R rows of ALD, padded)
-// transposed to dst[unit * ldT + row0 + r]: 8 consecutive rows of one unit
-// per 16-byte store, R / 8 consecutive threads on the consecutive pieces of
-// one unit (whole 128-byte lines per group of 8 lanes at R = 64)
-template <int R>
-__device__ __forceinline__ void store_act_tile_t(const bf16 *act, bf16 *__restrict__ dst, long long ldT,
-                                                 long long row0, int n, int tid) {
-  constexpr int P8 = R / 8;
-#pragma unroll 2
-  for (int e = tid; e < P8 * HID; e += 256) {
-    const int u = e / P8, r8 = (e % P8) * 8;
-    bf16 *o = dst + (long long)u * ldT + row0 + r8;
-    if (row0 + r8 + 8 <= n) {
-      bf16x8 pk;
-#pragma unroll
-      for (int k = 0; k < 8; ++k) pk[k] = act[(r8 + k) * ALD + u];
-      *reinterpret_cast<bf16x8 *>(o) = pk;
-    } else {
-      for (int k = 0; row0 + r8 + k < n; ++k) o[k] = act[(r8 + k) * ALD + u];
-    }
-  }
-}
-
-// What the training forward keeps for the backward pass, per row of the
-// batch (row-major [n][256] unless noted): the standardized features xf
-// [n][6], the pre-activations z1..z4 (FP32), the BF16 activations a1..a3
-// (the inputs of the BF16 layers) transposed, aT[l][unit * ldT + row] (the
-// weight-gradient products read them along the batch), and, instead of the
-// standardized outputs,
-// the loss term and its gradient dy [n][5] against the targets t (SoA 5 x
-// ld) with the row weights w (NULL = 1): per element d = y - (t - out_mean)
-// / out_std, the loss d^2, or for huber = delta > 0 the Huber function (d^2
-// up to |d| = delta, then 2 delta |d| - delta^2, gradient clipped to
-// 2 delta sign(d)), times the row weight; loss and gradient divided by n.
-struct TrainSink {
-  float *xf;
-  float *z[4];
-  bf16 *aT[3];
-  long long ldT;
-  const float *t;
-  long long ldt;
-  const float *w;
-  float huber;
-  float *dy;
-  float *loss;
-};
 
 // With idx != NULL, row r of the network is entry idx[r] for r < *count
 // (a compacted subset); otherwise row r is entry r, r < n.
@@ -1285,7 +821,7 @@ __global__ void __launch_bounds__(256, 2) k_mlp_fused(const float *__restrict__ 
       bf16x8 aop[4];
 #pragma unroll
       for (int ti = 0; ti < 4; ++ti)
-        aop[ti] = *reinterpret_cast<const bf16x8 *>(W + (ub + 16 * ti + c16) * HID + k0 + 8 * q);
+        aop[ti] = *reinterpret_cast<const bf16x8 *>(W + ((4 * w + ti) * (HID / 32) + k0 / 32) * 512 + 8 * lane);
 #pragma unroll
       for (int tj = 0; tj < 8; ++tj) {
         const bf16x8 bop = *reinterpret_cast<const bf16x8 *>(&act[(16 * tj + c16) * ALD + k0 + 8 * q]);
@@ -1365,207 +901,616 @@ __global__ void __launch_bounds__(256, 2) k_mlp_fused(const float *__restrict__ 
   }
 }
 
-// The training forward: the network of k_mlp_fused on a batch of n rows,
-// R rows per block, keeping what the backward pass reads (TrainSink), with
-// the loss and its output gradient in place of the outputs.
-constexpr int TR = 64;  // rows per block
-__global__ void __launch_bounds__(256, 2) k_mlp_train_fwd(const float *__restrict__ x6, long long ld, int n,
-                                                          const float *__restrict__ P, const bf16 *__restrict__ Wt,
-                                                          const float *__restrict__ sc, JobP jp, TrainSink ts) {
-  constexpr int R = TR;
-  constexpr int NT = R / 16;  // row tiles of 16
-  constexpr int ZLD = 64 + 4;  // padded rows of the pre-activation staging tiles
+// ---------------------------------------------------------------------------
+// Training: three launches make the gradient of a batch.
+//  1. k_mlp_train: forward and backward of the whole network for R rows at a
+//     time, activations and their gradients resident in one LDS tile, the
+//     SiLU derivatives of layers 1 to 3 (FP32) in registers. It leaves what
+//     the weight gradients are made of, a1..a3 and dz2..dz4 (BF16, row-major),
+//     and per block the sums over its rows of everything thin: W1, the biases,
+//     W5 and the loss.
+//  2. k_weight_grad: dW_l = a_{l-1}^T dz_l, the three layers in one launch, split
+//     over the rows.
+//  3. k_grad_reduce: adds up both kernels' partial sums (fixed order, no
+//     atomics: the same batch gives the same gradient bit for bit).
+// One launch per layer product (FP32 pre-activations and both layouts of
+// every dz through HBM, 0.9 GB at 65,536 rows, 14 launches) took 440 us for a
+// gradient and step at 65,536 rows and 134 us at 1000; this takes 209 and 34.
+// ---------------------------------------------------------------------------
+// columns of a block's row of partial sums: W1 and b1, b2, b3, then b4, W5, b5
+// (contiguous in the parameter vector each), and the loss's parts
+constexpr int PS_W1 = 0, PS_B1 = NIN * HID, PS_B2 = PS_B1 + HID, PS_B3 = PS_B2 + HID, PS_B4 = PS_B3 + HID,
+              PS_W5 = PS_B4 + HID, PS_B5 = PS_W5 + HID * NOUT, PS_LOSS = PS_B5 + NOUT, PS_N = PS_LOSS + 1;
+constexpr int PS_LD = (PS_N + 3) / 4 * 4;
+constexpr int TRAIN_THREADS = 512, TRAIN_BLOCKS = 256;  // one block per CU, taking tiles in turn
+static_assert(OFF_W5 == OFF_B4 + HID && OFF_B5 == OFF_W5 + HID * NOUT, "b4, W5, b5 are contiguous");
+
+// the parameter of a column (of PS_LOSS such)
+__device__ __forceinline__ long long thin_param(int col) {
+  return col < PS_B2 ? OFF_W1 + col
+         : col < PS_B3 ? OFF_B2 + (col - PS_B2)
+         : col < PS_B4 ? OFF_B3 + (col - PS_B3) : OFF_B4 + (col - PS_B4);
+}
+
+// The rows of a batch: targets t (SoA 5 x ldt) with row weights w (NULL = 1)
+// and what k_mlp_train leaves. Loss per element d = y - (t - out_mean) /
+// out_std: d^2, or for huber = delta > 0 the Huber function (d^2 up to |d| =
+// delta, then 2 delta |d| - delta^2, gradient clipped to 2 delta sign(d)),
+// times the row weight; loss and gradient divided by n.
+struct TrainSink {
+  const float *t;
+  long long ldt;
+  const float *w;
+  float huber;
+  bf16 *a[3], *dz[3];  // a1..a3 and dz2..dz4, [n][256]
+  float *part;         // [blocks][PS_LD]
+};
+
+// Sums over the 16 rows a DPP row of lanes holds, of 8 values per lane: each
+// fold adds two values over a pair of lanes and leaves one of the sums in
+// either, so that three levels of folds and one addition leave lane c16 the
+// sum of value t(c16), in 8 instead of 32 additions. Partners are lanes ^15,
+// ^7, ^3, ^1; bits 3, 2, 1 of the lane choose the value.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float x) {
+  return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(x), CTRL, 0xf, 0xf, true));
+}
+template <int CTRL>
+__device__ __forceinline__ float fold(float v0, float v1, bool upper) {
+  return (upper ? v1 : v0) + dpp<CTRL>(upper ? v0 : v1);
+}
+struct RowFold {
+  bool b3, b2, b1;
+  __device__ explicit RowFold(int c16) : b3(c16 & 8), b2(c16 & 4), b1(c16 & 2) {}
+  // units r = 0..3 of a unit tile, then both unit tiles of the wave
+  __device__ float units(const float v[4]) const {
+    return fold<0x141>(fold<0x140>(v[0], v[1], b3), fold<0x140>(v[2], v[3], b3), b2);
+  }
+  __device__ float tiles(const float v[2]) const {
+    const float s = fold<0x1B>(v[0], v[1], b1);
+    return s + dpp<0xB1>(s);
+  }
+  // the unit (of the wave's 32) whose sum this lane ends up with
+  __device__ int unit(int q) const { return 16 * b1 + 4 * q + b3 + 2 * b2; }
+};
+
+// Keeps loads and addresses of one phase of k_mlp_train in that phase: without
+// it the compiler moves everything the tile loop reads ahead of the loop and
+// spills 2.5 KB of registers per lane.
+template <typename T>
+using GlobalPtr = const __attribute__((address_space(1))) T *;
+template <typename T>
+__device__ __forceinline__ GlobalPtr<T> here(const T *p) {
+  asm volatile("" : "+s"(p));
+  return (GlobalPtr<T>)p;
+}
+// one register now: otherwise what it is computed from may be kept instead (z
+// and sigmoid(z) for a derivative that is needed much later)
+__device__ __forceinline__ float pin(float x) {
+  asm volatile("" : "+v"(x));
+  return x;
+}
+
+// the block's activation tile to rows row0.. of dst [n][256], 16 bytes per lane
+__device__ __forceinline__ void store_tile(const bf16 *act, bf16 *__restrict__ dst, long long row0, int rows,
+                                           int tid) {
+  const int c = 8 * (tid & 31);
+  bf16 *d = dst + row0 * HID + c;
+#pragma unroll 2
+  for (int r = tid >> 5; r < rows; r += TRAIN_THREADS / 32)
+    *reinterpret_cast<bf16x8 *>(d + r * HID) = *reinterpret_cast<const bf16x8 *>(&act[r * ALD + c]);
+}
+
+// One block of 8 waves per CU; R = 16 NT rows per tile. Products are computed
+// transposed as in the fused inference, wave w owning units 32 w..32 w + 31:
+// a lane's results are 4 consecutive units (u0 + 0..3) of one row (16 tj + c16)
+// per pair of tiles, and every elementwise step keeps that layout. What bounds
+// it is the chain of seven phases per tile between barriers, so that nothing
+// in it waits for memory: a wave's share of the next product's weights (64
+// registers) is loaded during the elementwise phase before it, the thin
+// parameters are in LDS, and inputs and targets of the next 512 rows are
+// fetched, and the inputs' sines and cosines taken, by all threads at once.
+// 65,536 rows: 143 us, of which the matrix products need 21 and the vector
+// instructions 54 (SiLU and its derivative, 5 exponentials and reciprocals
+// per unit and row); as 4 waves of 64 units with the weights loaded where
+// they are used, 250.
+template <int NT>
+__global__ void __launch_bounds__(TRAIN_THREADS, 2) k_mlp_train(const float *__restrict__ x6, long long ld, int n,
+                                                                const float *__restrict__ P, const bf16 *Wt,
+                                                                const bf16 *Wr, const float *__restrict__ sc,
+                                                                JobP jp, TrainSink ts) {
+  constexpr int R = 16 * NT, GT = TRAIN_THREADS / R, RED = R * NOUT;
   __shared__ __attribute__((aligned(16))) bf16 act[R * ALD];
-  __shared__ float xn[R * NIN];
-  __shared__ __attribute__((aligned(16))) float zs[4 * 16 * ZLD];  // one 16 x 64 tile per wave
-  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
-  const long long row0 = (long long)blockIdx.x * R;
-  if (row0 >= n) return;
-  // standardized input features of the tile (rows past n read as zeros)
-  if (tid < R) {
-    const long long i = row0 + tid;
-    float f[NIN] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    if (i < n) {
-      features(x6, ld, i, jp, f);
-#pragma unroll
-      for (int k = 0; k < NIN; ++k) f[k] = (f[k] - sc[S_INOFF + k]) * sc[S_INSCALE + k];
-#pragma unroll
-      for (int k = 0; k < NIN; ++k) ts.xf[i * NIN + k] = f[k];
-    }
-#pragma unroll
-    for (int k = 0; k < NIN; ++k) xn[tid * NIN + k] = f[k];
+  __shared__ __attribute__((aligned(16))) float th[PS_LD], ps[PS_LD];
+  __shared__ __attribute__((aligned(16))) float xn[TRAIN_THREADS * NIN], tn[TRAIN_THREADS * (NOUT + 1)];
+  __shared__ float red[8 * RED], dys[RED], lossp[NOUT];
+  for (int e = threadIdx.x; e < PS_LD; e += TRAIN_THREADS) {
+    th[e] = e < PS_LOSS ? P[thin_param(e)] : 0.0f;
+    ps[e] = 0.0f;
   }
-  __syncthreads();
-  {  // layer 1 (FP32): thread = pair of hidden units x half of the rows
-    const int u = 2 * (tid & 127), rb = (tid >> 7) * (R / 2);
-    float w0[NIN], w1[NIN];
+  if (threadIdx.x < NOUT) lossp[threadIdx.x] = 0.0f;
+  const int ntiles = (n + R - 1) / R;
+  int slot = GT;  // of the tile in the staged group
+  for (int tile = blockIdx.x; tile < ntiles; tile += gridDim.x, ++slot) {
+    int tid = threadIdx.x;
+    asm volatile("" : "+v"(tid));  // as for here(): no address leaves the loop
+    const int lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int q = lane >> 4, c16 = lane & 15, ub = 32 * w;
+    const RowFold rf(c16);
+    const int um = ub + rf.unit(q);       // the unit whose sums this lane has,
+    const bool keeps = (c16 & 1) == 0;    // and adds
+    if (slot == GT) {  // stage the inputs and targets of this and the next GT - 1 tiles
+      slot = 0;
+      const long long t = tile + (long long)(tid / R) * gridDim.x, i = t * R + tid % R;
+      float f[NIN] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f}, tg[NOUT + 1] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+      if (i < n) {
+        tg[NOUT] = ts.w ? ts.w[i] : 1.0f;
+        if (tg[NOUT] != 0.0f) {
 #pragma unroll
-    for (int k = 0; k < NIN; ++k) {
-      w0[k] = P[OFF_W1 + k * HID + u];
-      w1[k] = P[OFF_W1 + k * HID + u + 1];
-    }
-    const float b0 = P[OFF_B1 + u], b1 = P[OFF_B1 + u + 1];
-    for (int r = rb; r < rb + R / 2; ++r) {
-      float z0 = b0, z1 = b1;
+          for (int o = 0; o < NOUT; ++o) tg[o] = (ts.t[o * ts.ldt + i] - sc[S_OMEAN + o]) / sc[S_OSTD + o];
+        }
+        features(x6, ld, i, jp, f);
 #pragma unroll
-      for (int k = 0; k < NIN; ++k) {
-        z0 = fmaf(xn[r * NIN + k], w0[k], z0);
-        z1 = fmaf(xn[r * NIN + k], w1[k], z1);
+        for (int k = 0; k < NIN; ++k) f[k] = (f[k] - sc[S_INOFF + k]) * sc[S_INSCALE + k];
       }
-      bf16x2 pr;
-      pr[0] = (bf16)silu_f(z0);
-      pr[1] = (bf16)silu_f(z1);
-      *reinterpret_cast<bf16x2 *>(&act[r * ALD + u]) = pr;
-      if (row0 + r < n) *reinterpret_cast<float2 *>(&ts.z[0][(row0 + r) * HID + u]) = float2{z0, z1};
+#pragma unroll
+      for (int k = 0; k < NIN; ++k) xn[tid * NIN + k] = f[k];
+#pragma unroll
+      for (int o = 0; o <= NOUT; ++o) tn[tid * (NOUT + 1) + o] = tg[o];
     }
-  }
-  __syncthreads();
-  store_act_tile_t<R>(act, ts.aT[0], ts.ldT, row0, n, tid);
-  const int q = lane >> 4, c16 = lane & 15, ub = 64 * w;
-  const long long offb[3] = {OFF_B2, OFF_B3, OFF_B4};
-  f32x4 acc[4][NT];  // [unit tile][row tile]
-  for (int l = 0; l < 3; ++l) {
-    const bf16 *W = Wt + (long long)l * HID * HID;
+    const long long row0 = (long long)tile * R;
+    const int rows = (int)min((long long)R, n - row0);
+    bf16x8 wf[2][HID / 32];  // the wave's weights of the next product
+    const auto load_weights = [&](const bf16 *W) {
+      const GlobalPtr<bf16x8> p = (GlobalPtr<bf16x8>)here(W) + 2 * w * (HID / 32) * 64 + lane;
 #pragma unroll
-    for (int ti = 0; ti < 4; ++ti)
+      for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < NT; ++tj) acc[ti][tj] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int k0 = 0; k0 < HID; k0 += 32) {
-      bf16x8 aop[4];
+        for (int ks = 0; ks < HID / 32; ++ks) wf[ti][ks] = p[(ti * (HID / 32) + ks) * 64];
+    };
+    f32x4 acc[2][NT];  // [unit tile][row tile]
+    const auto product = [&]() {
 #pragma unroll
-      for (int ti = 0; ti < 4; ++ti)
-        aop[ti] = *reinterpret_cast<const bf16x8 *>(W + (ub + 16 * ti + c16) * HID + k0 + 8 * q);
+      for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < NT; ++tj) {
-        const bf16x8 bop = *reinterpret_cast<const bf16x8 *>(&act[(16 * tj + c16) * ALD + k0 + 8 * q]);
+        for (int tj = 0; tj < NT; ++tj) acc[ti][tj] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-        for (int ti = 0; ti < 4; ++ti)
-          acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aop[ti], bop, acc[ti][tj], 0, 0, 0);
-      }
-    }
-    __syncthreads();  // every wave has read the layer's input tile
+      for (int ks = 0; ks < HID / 32; ++ks)
+#pragma unroll
+        for (int tj = 0; tj < NT; ++tj) {
+          const bf16x8 bop = *reinterpret_cast<const bf16x8 *>(&act[(16 * tj + c16) * ALD + 32 * ks + 8 * q]);
+#pragma unroll
+          for (int ti = 0; ti < 2; ++ti)
+            acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ti][ks], bop, acc[ti][tj], 0, 0, 0);
+        }
+    };
+    const auto vec = [&](int col) { return *reinterpret_cast<const f32x4 *>(&th[col]); };
+    load_weights(Wt);
+    __syncthreads();
+    f32x4 ds1[2][NT], ds2[2][NT], ds3[2][NT];  // SiLU derivatives of layers 1 to 3
     {
-      // the pre-activations z = acc + bias of this layer: each 16-row tile
-      // of the wave's 64 units goes through the wave's own LDS tile, so
-      // that a store instruction writes 4 rows x 256 contiguous bytes
-      // (whole lines) instead of 16 rows x 64 bytes. One wave writes and
-      // reads its tile; its LDS operations complete in order, and the wave
-      // barrier keeps the compiler from moving them across each other.
-      float *zl = ts.z[l + 1] + row0 * HID;  // the block's rows (32-bit offsets from here)
-      float *zw = zs + w * 16 * ZLD;
+      float xr[NT][NIN];
 #pragma unroll
-      for (int tj = 0; tj < NT; ++tj) {
+      for (int tj = 0; tj < NT; ++tj)
 #pragma unroll
-        for (int ti = 0; ti < 4; ++ti) {
-          const float4 bb = *reinterpret_cast<const float4 *>(&P[offb[l] + ub + 16 * ti + 4 * q]);
-          *reinterpret_cast<float4 *>(&zw[c16 * ZLD + 16 * ti + 4 * q]) =
-              float4{acc[ti][tj][0] + bb.x, acc[ti][tj][1] + bb.y, acc[ti][tj][2] + bb.z, acc[ti][tj][3] + bb.w};
-        }
-        __builtin_amdgcn_wave_barrier();
+        for (int k = 0; k < NIN; ++k) xr[tj][k] = xn[(slot * R + 16 * tj + c16) * NIN + k];
 #pragma unroll
-        for (int rr = 0; rr < 4; ++rr) {
-          const int rl = 4 * rr + (lane >> 4), r = 16 * tj + rl;
-          const float4 v = *reinterpret_cast<const float4 *>(&zw[rl * ZLD + 4 * c16]);
-          if (row0 + r < n) *reinterpret_cast<float4 *>(&zl[r * HID + ub + 4 * c16]) = v;
-        }
-        __builtin_amdgcn_wave_barrier();
-      }
-    }
-    if (l < 2) {
+      for (int ti = 0; ti < 2; ++ti) {
+        const int u0 = ub + 16 * ti + 4 * q;
+        const f32x4 b = vec(PS_B1 + u0);
+        f32x4 w1[NIN];
 #pragma unroll
-      for (int ti = 0; ti < 4; ++ti) {
-        const int u0 = ub + 16 * ti + 4 * q;  // this lane's 4 consecutive units
-        float bias[4];
-#pragma unroll
-        for (int r = 0; r < 4; ++r) bias[r] = P[offb[l] + u0 + r];
+        for (int k = 0; k < NIN; ++k) w1[k] = vec(PS_W1 + k * HID + u0);
 #pragma unroll
         for (int tj = 0; tj < NT; ++tj) {
           bf16x4 pk;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) pk[r] = (bf16)silu_f(acc[ti][tj][r] + bias[r]);
+          for (int r = 0; r < 4; ++r) {
+            float z = b[r];
+#pragma unroll
+            for (int k = 0; k < NIN; ++k) z = fmaf(xr[tj][k], w1[k][r], z);
+            const float s = sigmoid_f(z);
+            pk[r] = (bf16)(z * s);
+            ds1[ti][tj][r] = pin(s * (1.0f + z * (1.0f - s)));
+          }
+          *reinterpret_cast<bf16x4 *>(&act[(16 * tj + c16) * ALD + u0]) = pk;
+        }
+      }
+    }
+    __syncthreads();
+    const auto hidden = [&](bf16 *a, const bf16 *next, int bias_col, f32x4 (&ds)[2][NT]) {
+      store_tile(act, a, row0, rows, tid);
+      product();
+      load_weights(next);
+      __syncthreads();  // every wave has read the layer's input tile
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti) {
+        const int u0 = ub + 16 * ti + 4 * q;
+        const f32x4 bias = vec(bias_col + u0);
+#pragma unroll
+        for (int tj = 0; tj < NT; ++tj) {
+          bf16x4 pk;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float z = acc[ti][tj][r] + bias[r], s = sigmoid_f(z);
+            pk[r] = (bf16)(z * s);
+            ds[ti][tj][r] = pin(s * (1.0f + z * (1.0f - s)));
+          }
           *reinterpret_cast<bf16x4 *>(&act[(16 * tj + c16) * ALD + u0]) = pk;
         }
       }
       __syncthreads();
-      store_act_tile_t<R>(act, ts.aT[l + 1], ts.ldT, row0, n, tid);
-    } else {
-      // layer 5 (FP32) on a4 = silu(z4): partial sums over this lane's 16
-      // units for each of its 8 rows, then over the 4 lane groups
+    };
+    hidden(ts.a[0], Wt + HID * HID, PS_B2, ds2);
+    hidden(ts.a[1], Wt + 2 * HID * HID, PS_B3, ds3);
+    store_tile(act, ts.a[2], row0, rows, tid);
+    product();
+    {
+      // layer 5 (FP32) on a4 = silu(z4): partial sums over this lane's 8
+      // units for each of its rows, then over the 4 lane groups and 8 waves
       float s5[NT][NOUT];
 #pragma unroll
       for (int tj = 0; tj < NT; ++tj)
 #pragma unroll
         for (int o = 0; o < NOUT; ++o) s5[tj][o] = 0.0f;
 #pragma unroll
-      for (int ti = 0; ti < 4; ++ti) {
+      for (int ti = 0; ti < 2; ++ti) {
         const int u0 = ub + 16 * ti + 4 * q;
-        float bias[4], w5[4][NOUT];
+        const f32x4 bias = vec(PS_B4 + u0);
+        f32x4 w5[NOUT];  // the 4 x 5 weights of units u0 + 0..3 in memory order
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          bias[r] = P[offb[l] + u0 + r];
+        for (int o = 0; o < NOUT; ++o) w5[o] = vec(PS_W5 + u0 * NOUT + 4 * o);
 #pragma unroll
-          for (int o = 0; o < NOUT; ++o) w5[r][o] = P[OFF_W5 + (u0 + r) * NOUT + o];
-        }
+        for (int r = 0; r < 4; ++r)
 #pragma unroll
-        for (int tj = 0; tj < NT; ++tj)
+          for (int tj = 0; tj < NT; ++tj) {
+            const float z = acc[ti][tj][r] + bias[r];
+            acc[ti][tj][r] = pin(z);  // z4, kept for the way back
+            const float a4 = silu_f(z);
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float a4 = silu_f(acc[ti][tj][r] + bias[r]);
-#pragma unroll
-            for (int o = 0; o < NOUT; ++o) s5[tj][o] = fmaf(a4, w5[r][o], s5[tj][o]);
+            for (int o = 0; o < NOUT; ++o)
+              s5[tj][o] = fmaf(a4, w5[(r * NOUT + o) / 4][(r * NOUT + o) % 4], s5[tj][o]);
           }
       }
-      float *red = reinterpret_cast<float *>(act);  // [4 waves][R][NOUT]
 #pragma unroll
-      for (int tj = 0; tj < NT; ++tj) {
+      for (int tj = 0; tj < NT; ++tj)
 #pragma unroll
         for (int o = 0; o < NOUT; ++o) {
           s5[tj][o] += __shfl_xor(s5[tj][o], 16);
           s5[tj][o] += __shfl_xor(s5[tj][o], 32);
+          if (q == 0) red[w * RED + (16 * tj + c16) * NOUT + o] = s5[tj][o];
         }
-        if (q == 0) {
+    }
+    load_weights(Wr + 2 * HID * HID);
+    __syncthreads();
+    if (tid < RED) {  // outputs, loss and dy: thread = output x row
+      const int o = tid / R, row = tid % R, e = row * NOUT + o;
+      float v[8], l = 0.0f, g = 0.0f;
 #pragma unroll
-          for (int o = 0; o < NOUT; ++o) red[(w * R + 16 * tj + c16) * NOUT + o] = s5[tj][o];
-        }
-      }
-      __syncthreads();
-      float lrow = 0.0f;
-      if (tid < R) {
-        const long long i = row0 + tid;
-        if (i < n) {
-#pragma unroll
-          for (int o = 0; o < NOUT; ++o) {
-            const float y = P[OFF_B5 + o] + ((red[(0 * R + tid) * NOUT + o] + red[(1 * R + tid) * NOUT + o]) +
-                                             (red[(2 * R + tid) * NOUT + o] + red[(3 * R + tid) * NOUT + o]));
-            {
-              // the loss term and its gradient (see TrainSink)
-              const float wr = ts.w ? ts.w[i] : 1.0f;
-              float g = 0.f;
-              if (wr != 0.0f) {
-                const float tn = (ts.t[o * ts.ldt + i] - sc[S_OMEAN + o]) / sc[S_OSTD + o];
-                const float d = y - tn;
-                if (ts.huber > 0.0f && fabsf(d) > ts.huber) {
-                  lrow += wr * (2.0f * ts.huber * fabsf(d) - ts.huber * ts.huber);
-                  g = 2.0f * wr * copysignf(ts.huber, d);
-                } else {
-                  lrow += wr * d * d;
-                  g = 2.0f * wr * d;
-                }
-              }
-              ts.dy[i * NOUT + o] = g / (float)n;
-            }
-          }
+      for (int k = 0; k < 8; ++k) v[k] = red[k * RED + e];
+      const float y = th[PS_B5 + o] + (((v[0] + v[1]) + (v[2] + v[3])) + ((v[4] + v[5]) + (v[6] + v[7])));
+      const float *tr = &tn[(slot * R + row) * (NOUT + 1)];
+      const float wrow = tr[NOUT];
+      if (wrow != 0.0f) {
+        const float d = y - tr[o];
+        if (ts.huber > 0.0f && fabsf(d) > ts.huber) {
+          l = wrow * (2.0f * ts.huber * fabsf(d) - ts.huber * ts.huber);
+          g = 2.0f * wrow * copysignf(ts.huber, d);
+        } else {
+          l = wrow * d * d;
+          g = 2.0f * wrow * d;
         }
       }
-      {
-        // block sum of the loss terms (rows of the first R / 64 waves)
+      l = l / (float)n;
+      g = g / (float)n;
+      dys[e] = g;
 #pragma unroll
-        for (int off = 32; off > 0; off >>= 1) lrow += __shfl_xor(lrow, off);
-        if (lane == 0 && w < R / 64) atomicAdd(ts.loss, lrow / (float)n);
+      for (int off = R / 2; off > 0; off >>= 1) {
+        l += __shfl_xor(l, off);
+        g += __shfl_xor(g, off);
+      }
+      if (row == 0) {
+        lossp[o] += l;
+        ps[PS_B5 + o] += g;
       }
     }
+    __syncthreads();
+    // layer 5 backwards: dz4 = (dy W5^T) silu'(z4), dW5 = a4^T dy, db4 = sum dz4
+    {
+      float dy[NT][NOUT], sz[2], sw[NOUT][2];
+#pragma unroll
+      for (int tj = 0; tj < NT; ++tj)
+#pragma unroll
+        for (int o = 0; o < NOUT; ++o) dy[tj][o] = dys[(16 * tj + c16) * NOUT + o];
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti) {
+        const int u0 = ub + 16 * ti + 4 * q;
+        bf16x4 pk[NT];
+        float gw[NOUT][4], gz[4];
+        f32x4 w5[NOUT];
+#pragma unroll
+        for (int o = 0; o < NOUT; ++o) w5[o] = vec(PS_W5 + u0 * NOUT + 4 * o);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          gz[r] = 0.0f;
+#pragma unroll
+          for (int o = 0; o < NOUT; ++o) gw[o][r] = 0.0f;
+#pragma unroll
+          for (int tj = 0; tj < NT; ++tj) {
+            const float z = acc[ti][tj][r], s = sigmoid_f(z), a4 = z * s;
+            float da = 0.f;
+#pragma unroll
+            for (int o = 0; o < NOUT; ++o) {
+              da = fmaf(dy[tj][o], w5[(r * NOUT + o) / 4][(r * NOUT + o) % 4], da);
+              gw[o][r] = fmaf(a4, dy[tj][o], gw[o][r]);
+            }
+            const float g = da * (s * (1.0f + z * (1.0f - s)));
+            gz[r] += g;
+            pk[tj][r] = (bf16)g;
+          }
+        }
+        sz[ti] = rf.units(gz);
+#pragma unroll
+        for (int o = 0; o < NOUT; ++o) sw[o][ti] = rf.units(gw[o]);
+#pragma unroll
+        for (int tj = 0; tj < NT; ++tj) *reinterpret_cast<bf16x4 *>(&act[(16 * tj + c16) * ALD + u0]) = pk[tj];
+      }
+      const float s = rf.tiles(sz);
+      if (keeps) ps[PS_B4 + um] += s;
+#pragma unroll
+      for (int o = 0; o < NOUT; ++o) {
+        const float so = rf.tiles(sw[o]);
+        if (keeps) ps[PS_W5 + um * NOUT + o] += so;
+      }
+    }
+    __syncthreads();
+    // hidden layers: dz_l = (dz_{l+1} W_{l+1}^T) silu'(z_l), db_l = sum dz_l
+    const auto hidden_back = [&](bf16 *dz, const bf16 *next, int sums, const f32x4 (&ds)[2][NT]) {
+      store_tile(act, dz, row0, rows, tid);
+      product();
+      load_weights(next);
+      __syncthreads();
+      float sz[2];
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti) {
+        const int u0 = ub + 16 * ti + 4 * q;
+        float gz[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int tj = 0; tj < NT; ++tj) {
+          bf16x4 pk;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            const float g = acc[ti][tj][r] * ds[ti][tj][r];
+            gz[r] += g;
+            pk[r] = (bf16)g;
+          }
+          *reinterpret_cast<bf16x4 *>(&act[(16 * tj + c16) * ALD + u0]) = pk;
+        }
+        sz[ti] = rf.units(gz);
+      }
+      const float s = rf.tiles(sz);
+      if (keeps) ps[sums + um] += s;
+      __syncthreads();
+    };
+    hidden_back(ts.dz[2], Wr + HID * HID, PS_B3, ds3);
+    hidden_back(ts.dz[1], Wr, PS_B2, ds2);
+    // dz1 never leaves its registers: dW1 = x^T dz1, db1 = sum dz1
+    store_tile(act, ts.dz[0], row0, rows, tid);
+    product();
+    {
+      float xr[NT][NIN], sz[2], sw[NIN][2];
+#pragma unroll
+      for (int tj = 0; tj < NT; ++tj)
+#pragma unroll
+        for (int k = 0; k < NIN; ++k) xr[tj][k] = xn[(slot * R + 16 * tj + c16) * NIN + k];
+#pragma unroll
+      for (int ti = 0; ti < 2; ++ti) {
+        float gw[NIN][4], gz[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          gz[r] = 0.0f;
+#pragma unroll
+          for (int k = 0; k < NIN; ++k) gw[k][r] = 0.0f;
+#pragma unroll
+          for (int tj = 0; tj < NT; ++tj) {
+            const float g = acc[ti][tj][r] * ds1[ti][tj][r];
+            gz[r] += g;
+#pragma unroll
+            for (int k = 0; k < NIN; ++k) gw[k][r] = fmaf(xr[tj][k], g, gw[k][r]);
+          }
+        }
+        sz[ti] = rf.units(gz);
+#pragma unroll
+        for (int k = 0; k < NIN; ++k) sw[k][ti] = rf.units(gw[k]);
+      }
+      const float s = rf.tiles(sz);
+      if (keeps) ps[PS_B1 + um] += s;
+#pragma unroll
+      for (int k = 0; k < NIN; ++k) {
+        const float sk = rf.tiles(sw[k]);
+        if (keeps) ps[PS_W1 + k * HID + um] += sk;
+      }
+    }
+    __syncthreads();  // act, xn and dys are free for the next tile
   }
+  float *out = ts.part + (long long)blockIdx.x * PS_LD;
+  for (int e = threadIdx.x; e < PS_LOSS; e += TRAIN_THREADS) out[e] = ps[e];
+  if (threadIdx.x == 0) out[PS_LOSS] = ((lossp[0] + lossp[1]) + (lossp[2] + lossp[3])) + lossp[4];
+}
+
+// dW_l(i, j) = sum over rows of a_{l-1}(row, i) dz_l(row, j) for l = 2..4: 128 x
+// 128 tiles, 4 waves of 64 x 64, rows in steps of 64 through double-buffered
+// LDS, split over the rows. Both operands are row-major, rows being the sum
+// index; an MFMA lane needs 8 consecutive rows of one unit, which two
+// transposing LDS reads give (ds_read_b64_tr_b16: 16 lanes fetch a 4 x 16
+// block, 4 units each, and lane i gets unit i of the 4 rows), so no transposed
+// copy of either exists in memory. The 4 tiles of a (layer, split) are next to
+// each other on one XCD, whose L2 then reads each operand from memory once:
+// 65,536 rows (0.2 GB) take 40 us, and 62 where those tiles are on different
+// XCDs. The transposing reads (64 bytes a clock) bound the rest.
+constexpr int WG_T = 128, WG_K = 64, WG_LD = WG_T + 16, WG_TILES = 4, WG_SPLITS = 42;
+struct WGrad {
+  const bf16 *a[3], *dz[3];
+  float *part;  // [split][layer][256 * 256]
+  int n, kchunk, tiles;
+};
+
+// 64 rows from k0 of 128 columns, rows past kend as zeros: a buffer load checks
+// its offset against the resource's size, so that the loop has no branches
+typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ void wg_load(u32x4 v[4], const bf16 *src, int k0, int kend, int col0, int tid) {
+  // (all uniform; said so, as the compiler takes vector instructions for parts of it)
+  const int rows = __builtin_amdgcn_readfirstlane(max(0, min(WG_K, kend - k0)));
+  const unsigned long long base = (unsigned long long)(src + (long long)k0 * HID);
+  const unsigned lo = __builtin_amdgcn_readfirstlane((unsigned)base);
+  const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(base >> 32));
+  const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+      (void *)((unsigned long long)hi << 32 | lo), 0, rows * HID * (int)sizeof(bf16), 0x00027000);
+  const int off = ((tid >> 4) * HID + 8 * (tid & 15)) * (int)sizeof(bf16);
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+    v[p] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, (16 * p * HID + col0) * (int)sizeof(bf16), 0);
+}
+
+__device__ __forceinline__ void wg_store(bf16 *T, const u32x4 v[4], int tid) {
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+    *reinterpret_cast<u32x4 *>(&T[(16 * p + (tid >> 4)) * WG_LD + 8 * (tid & 15)]) = v[p];
+}
+
+// 8 rows of unit u0 + c16 for lane (q, c16): k0 + 4 q + 0..3 and k0 + 16 + 4 q +
+// 0..3. Which k of the product's 32 a lane holds is free as long as both
+// operands agree, and 16 consecutive rows a read fall in distinct banks.
+__device__ __forceinline__ bf16x8 wg_operand(const bf16 *T, int k0, int u0, int q, int c16) {
+  typedef short s16x4 __attribute__((ext_vector_type(4)));
+  typedef short s16x8 __attribute__((ext_vector_type(8)));
+  typedef __attribute__((address_space(3))) s16x4 *LdsPtr;
+  const bf16 *p = &T[(k0 + 4 * q + (c16 >> 2)) * WG_LD + u0 + 4 * (c16 & 3)];
+  const s16x4 lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsPtr)p);
+  const s16x4 hi = __builtin_amdgcn_ds_read_tr16_b64_v4i16((LdsPtr)(p + 16 * WG_LD));
+  return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, hi, 0, 1, 2, 3, 4, 5, 6, 7));
+}
+
+__global__ void __launch_bounds__(256, 2) k_weight_grad(WGrad g) {
+  __shared__ __attribute__((aligned(16))) bf16 sm[2][2][WG_K * WG_LD];
+  const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6, q = lane >> 4, c16 = lane & 15;
+  // an eighth of the tiles per XCD (consecutive blocks go to different ones)
+  const unsigned t = (blockIdx.x & 7) * (gridDim.x >> 3) + (blockIdx.x >> 3);
+  if (t >= (unsigned)g.tiles) return;
+  const int tile = (int)(t % WG_TILES), ls = __builtin_amdgcn_readfirstlane((int)(t / WG_TILES));
+  const int split = __builtin_amdgcn_readfirstlane(ls / 3), layer = ls - 3 * split;
+  const int i0 = (tile >> 1) * WG_T, j0 = (tile & 1) * WG_T, im = 64 * (w >> 1), jm = 64 * (w & 1);
+  const int kbeg = split * g.kchunk, kend = min(g.n, kbeg + g.kchunk);
+  const bf16 *A = layer == 0 ? g.a[0] : (layer == 1 ? g.a[1] : g.a[2]);
+  const bf16 *B = layer == 0 ? g.dz[0] : (layer == 1 ? g.dz[1] : g.dz[2]);
+  f32x4 acc[4][4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j) acc[i][j] = f32x4{0.f, 0.f, 0.f, 0.f};
+  const int nk = (kend - kbeg + WG_K - 1) / WG_K;
+  // two steps in flight (rows past kend read as zeros, so that an odd number
+  // of steps adds an empty one)
+  u32x4 ra[2][4], rb[2][4];
+#pragma unroll
+  for (int p = 0; p < 2; ++p) {
+    wg_load(ra[p], A, kbeg + p * WG_K, kend, i0, tid);
+    wg_load(rb[p], B, kbeg + p * WG_K, kend, j0, tid);
+  }
+  for (int it = 0; it < nk; it += 2)
+#pragma unroll
+    for (int p = 0; p < 2; ++p) {
+      bf16 *As = sm[p][0], *Bs = sm[p][1];
+      wg_store(As, ra[p], tid);
+      wg_store(Bs, rb[p], tid);
+      __syncthreads();  // also: every wave is done with the stage's previous use
+      wg_load(ra[p], A, kbeg + (it + 2 + p) * WG_K, kend, i0, tid);
+      wg_load(rb[p], B, kbeg + (it + 2 + p) * WG_K, kend, j0, tid);
+      __builtin_amdgcn_sched_barrier(0);  // issued before the products, not after them
+#pragma unroll
+      for (int ks = 0; ks < WG_K; ks += 32) {
+        bf16x8 af[4], bf_[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+          af[i] = wg_operand(As, ks, im + 16 * i, q, c16);
+          bf_[i] = wg_operand(Bs, ks, jm + 16 * i, q, c16);
+        }
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+#pragma unroll
+          for (int j = 0; j < 4; ++j)
+            acc[i][j] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(af[i], bf_[j], acc[i][j], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+  // lane holds D[4 q + r][c16] of each tile
+  float *o = g.part + ((long long)split * 3 + layer) * HID * HID;
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int r = 0; r < 4; ++r)
+        o[(i0 + im + 16 * i + 4 * q + r) * HID + j0 + jm + 16 * j + c16] = acc[i][j][r];
+}
+
+// The gradient from the partial sums: blocks 0..191 the 3 x 256 x 256 weights
+// of the hidden layers (256 float4 columns x 4 groups of splits), the others 64
+// of the thin columns each (x 16 groups of blocks). G, and where the caller
+// asks for them its gradient vector and loss.
+constexpr int GR_THREADS = 1024, GR_WBLOCKS = 3 * HID * HID / 1024, GR_BLOCKS = GR_WBLOCKS + (PS_N + 63) / 64;
+__global__ void __launch_bounds__(GR_THREADS) k_grad_reduce(const float *__restrict__ wpart, int splits,
+                                                            const float *__restrict__ part, int blocks,
+                                                            float *__restrict__ G, float *__restrict__ grads,
+                                                            float *__restrict__ loss, float *__restrict__ loss_out) {
+  __shared__ float4 sh4[3][256];
+  __shared__ float sh[16][64];
+  const int tid = threadIdx.x;
+  if (blockIdx.x < GR_WBLOCKS) {
+    const int c = tid & 255, grp = tid >> 8;
+    const long long e = (long long)blockIdx.x * 1024 + 4 * c;
+    float4 s = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll 4
+    for (int k = grp; k < splits; k += 4) {
+      const float4 v = *reinterpret_cast<const float4 *>(&wpart[(long long)k * 3 * HID * HID + e]);
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+    if (grp) sh4[grp - 1][c] = s;
+    __syncthreads();
+    if (grp) return;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      const float4 v = sh4[k][c];
+      s.x += v.x; s.y += v.y; s.z += v.z; s.w += v.w;
+    }
+    const long long l = e / (HID * HID), off = l == 0 ? OFF_W2 : (l == 1 ? OFF_W3 : OFF_W4);
+    const long long o = off + e % (HID * HID);
+    *reinterpret_cast<float4 *>(&G[o]) = s;
+    if (grads) {  // a caller's vector need not be 16-byte aligned
+      grads[o] = s.x; grads[o + 1] = s.y; grads[o + 2] = s.z; grads[o + 3] = s.w;
+    }
+    return;
+  }
+  const int c = tid & 63, grp = tid >> 6, col = (blockIdx.x - GR_WBLOCKS) * 64 + c;
+  float s = 0.f;
+  if (col < PS_N) {
+#pragma unroll 4
+    for (int k = grp; k < blocks; k += 16) s += part[(long long)k * PS_LD + col];
+  }
+  sh[grp][c] = s;
+  __syncthreads();
+  if (grp || col >= PS_N) return;
+  s = 0.f;
+#pragma unroll
+  for (int k = 0; k < 16; ++k) s += sh[k][c];
+  if (col == PS_LOSS) {
+    *loss = s;
+    if (loss_out) *loss_out = s;
+    return;
+  }
+  const long long o = thin_param(col);
+  G[o] = s;
+  if (grads) grads[o] = s;
 }
 
 // error of the decoded prediction against the exact exit, per trust-map cell:
@@ -1658,16 +1603,10 @@ struct rt_model_s {
   // activations for up to `cap` rows
   long long cap = 0;
   void *act = nullptr;
-  float *z[4] = {nullptr, nullptr, nullptr, nullptr};  // hidden pre-activations (FP32)
-  bf16 *aT[3] = {nullptr, nullptr, nullptr};           // a1..a3 (BF16), transposed [256][ldT]
-  long long ldT = 0;                                   // row stride of the transposed arrays
-  float *p5 = nullptr;                                 // layer-5 gradient partials [L5_MAXB][L5_LD]
-  float *dy = nullptr;                                 // [cap][5]
-  bf16 *dzb[2] = {nullptr, nullptr};                   // BF16 dz [cap][256], ping-pong
-  bf16 *dzT[2] = {nullptr, nullptr};                   // their transposes [256][ldT]
-  float *xf = nullptr;                                 // standardized input features [cap][6]
-  float *wpart = nullptr;                              // split-K partial weight gradients [64][256 * 256]
-  float *cpart = nullptr;                              // per-row-tile column-sum partials [cap / 64][7][256]
+  bf16 *a[3] = {nullptr, nullptr, nullptr};   // a1..a3 [cap][256]
+  bf16 *dz[3] = {nullptr, nullptr, nullptr};  // dz2..dz4 [cap][256]
+  float *part = nullptr;                      // thin partial sums [TRAIN_BLOCKS][PS_LD]
+  float *wpart = nullptr;                     // weight-gradient partial sums [WG_SPLITS][3][256 * 256]
   // standardized outputs of the fused inference kernel, and the compacted
   // entry list of the gated inference
   long long ycap = 0;
@@ -1688,12 +1627,9 @@ int reserve_acts(rt_model mo, long long n) {
   }
   const long long cap = std::max(n, 4096LL);
   auto al = [](size_t x) { return (x + 255) & ~(size_t)255; };
-  const long long ldT = (cap + 63) & ~63LL;
-  const size_t zb = al(sizeof(float) * cap * HID), ab = al(sizeof(bf16) * ldT * HID);
-  const size_t yb = al(sizeof(float) * cap * NOUT), fb = al(sizeof(float) * cap * NIN);
-  const size_t pb = al(sizeof(float) * L5_MAXB * L5_LD);
-  const size_t wb = al(sizeof(float) * 64 * HID * HID), cb = al(sizeof(float) * ((cap + 63) / 64) * (NIN + 1) * HID);
-  const size_t bytes = 4 * zb + 3 * ab + yb + 4 * ab + fb + pb + wb + cb;
+  const size_t ab = al(sizeof(bf16) * cap * HID), pb = al(sizeof(float) * TRAIN_BLOCKS * PS_LD);
+  const size_t wb = al(sizeof(float) * WG_SPLITS * 3 * HID * HID);
+  const size_t bytes = 6 * ab + pb + wb;
   void *p = nullptr;
   if (hipMalloc(&p, bytes) != hipSuccess) {
     (void)hipGetLastError();
@@ -1701,18 +1637,10 @@ int reserve_acts(rt_model mo, long long n) {
   }
   char *c = (char *)p;
   size_t off = 0;
-  for (int l = 0; l < 4; ++l) { mo->z[l] = (float *)(c + off); off += zb; }
-  for (int l = 0; l < 3; ++l) { mo->aT[l] = (bf16 *)(c + off); off += ab; }
-  mo->ldT = ldT;
-  mo->dy = (float *)(c + off); off += yb;
-  mo->dzb[0] = (bf16 *)(c + off); off += ab;
-  mo->dzb[1] = (bf16 *)(c + off); off += ab;
-  mo->dzT[0] = (bf16 *)(c + off); off += ab;
-  mo->dzT[1] = (bf16 *)(c + off); off += ab;
-  mo->xf = (float *)(c + off); off += fb;
-  mo->p5 = (float *)(c + off); off += pb;
-  mo->wpart = (float *)(c + off); off += wb;
-  mo->cpart = (float *)(c + off); off += cb;
+  for (int l = 0; l < 3; ++l) { mo->a[l] = (bf16 *)(c + off); off += ab; }
+  for (int l = 0; l < 3; ++l) { mo->dz[l] = (bf16 *)(c + off); off += ab; }
+  mo->part = (float *)(c + off); off += pb;
+  mo->wpart = (float *)(c + off);
   mo->act = p;
   mo->cap = cap;
   return RT_OK;
@@ -1754,77 +1682,35 @@ void infer_outputs(rt_model mo, const float *x, long long ld, int n, hipStream_t
                      mo->scal, job_for(mo, nullptr), mo->yinf);
 }
 
-// returns the number of K splits used (EPI_SPLIT writes that many partials)
-int gemm(hipStream_t s, const bf16 *A, long long lda, const bf16 *B, long long ldb, int M, int N, int K, int epi,
-         const float *Z, long long ldz, float *Cf, long long ldcf, bf16 *Cb, long long ldcb, int splits = 1,
-         float *colsum = nullptr, bf16 *Cbt = nullptr, long long ldcbt = 0, const float *xf = nullptr) {
-  int kchunk = (K + splits - 1) / splits;
-  kchunk = (kchunk + GK - 1) / GK * GK;  // splits start on a K step
-  splits = (K + kchunk - 1) / kchunk;
-  const int nct = (int)gblocks(N, GT), nrt = (int)gblocks(M, GT);
-  const bool veca = lda % 8 == 0 && reinterpret_cast<uintptr_t>(A) % 16 == 0;
-  const bool vecb = ldb % 8 == 0 && reinterpret_cast<uintptr_t>(B) % 16 == 0;
-  Gemm g{A, lda, B, ldb, veca, vecb, M, N, K, kchunk, epi, nct, nrt, Z, ldz, Cf, ldcf, Cb, ldcb, colsum, xf, Cbt, ldcbt};
-  // 64 x 64 block tiles: 128 x 128 ones measured slower on the training
-  // shapes, whose time goes to the epilogue's activation traffic rather than
-  // to the MFMAs
-  hipLaunchKernelGGL(k_gemm, dim3((unsigned)((long long)nct * nrt * splits)), dim3(256), 0, s, g);
-  return splits;
-}
+// BF16 weights of W2 (l = 0), W3 (1), W4 (2) for the backward products (mo->Pb: forward)
+const bf16 *wr(rt_model mo) { return mo->Pb + NBF; }
 
-// BF16 weights of W2 (l = 0), W3 (1), W4 (2): transposed [out][in] and row-major [in][out]
-const bf16 *wb(rt_model mo, int l) { return mo->Pb + (long long)l * HID * HID; }
-const bf16 *wr(rt_model mo, int l) { return mo->Pb + NBF + (long long)l * HID * HID; }
-
-int split_for(int n) { return std::min(64, std::max(1, n / 512)); }
-
-// training forward of n rows (the fused network, keeping xf, z1..z4 and
-// a1..a3 for the backward pass) with the loss and its output gradient dy;
-// then the gradients of that loss into mo->G, the loss into scal[S_LOSS]
+// gradient and loss of a batch of n rows into mo->G and scal[S_LOSS], and to
+// the caller's vectors (may be NULL)
 void forward_backward(rt_model mo, const float *x, const float *t, long long ld, const float *wrow, int n,
-                      float huber, hipStream_t s) {
-  float *loss = mo->scal + S_LOSS;
-  hipLaunchKernelGGL(k_fill, dim3(gblocks(NPARAM, 256)), dim3(256), 0, s, mo->G, NPARAM, 0.0f);
-  hipLaunchKernelGGL(k_fill, dim3(1), dim3(64), 0, s, loss, 1LL, 0.0f);
-  const long long ldT = mo->ldT;
-  TrainSink ts{mo->xf, {mo->z[0], mo->z[1], mo->z[2], mo->z[3]}, {mo->aT[0], mo->aT[1], mo->aT[2]}, ldT, t, ld,
-               wrow, huber, mo->dy, loss};
-  hipLaunchKernelGGL(k_mlp_train_fwd, dim3(gblocks(n, TR)), dim3(256), 0, s, x, ld, n, mo->P, mo->Pb, mo->scal,
+                      float huber, float *grads, float *loss, hipStream_t s) {
+  TrainSink ts{t, ld, wrow, huber, {mo->a[0], mo->a[1], mo->a[2]}, {mo->dz[0], mo->dz[1], mo->dz[2]}, mo->part};
+  // Rows per tile: the fewest whose tiles go over the chip once, as a tile's
+  // chain of layers takes 21, 25 and 35 us at 16, 32 and 64 rows and the work
+  // beyond it shares the CU no better; past 8192 rows, 64, which read the
+  // weights least often. Gradient and step at 4096 / 8192 / 16384 / 65536 rows,
+  // us: 44 / 59 / 90 / 276 with 16, 49 / 51 / 76 / 216 with 32, 60 / 61 / 71 /
+  // 196 with 64.
+  const int rows = n <= 16 * TRAIN_BLOCKS ? 16 : n <= 32 * TRAIN_BLOCKS ? 32 : 64;
+  const int blocks = std::min((int)gblocks(n, rows), TRAIN_BLOCKS);
+  const auto kern = rows == 64 ? k_mlp_train<4> : rows == 32 ? k_mlp_train<2> : k_mlp_train<1>;
+  hipLaunchKernelGGL(kern, dim3(blocks), dim3(TRAIN_THREADS), 0, s, x, ld, n, mo->P, mo->Pb, wr(mo), mo->scal,
                      job_for(mo, nullptr), ts);
-  // layer 5: its per-element work (dz of layer 4) is as large as a hidden
-  // layer's and parallel over rows: one block per 64 rows, up to 1024
-  // blocks; the blocks' partial sums of the layer-5 weights and biases and
-  // of b4 are added in a second pass
-  const int l5_grid = std::min(L5_MAXB, (int)gblocks(n, 64));
-  hipLaunchKernelGGL(k_layer5_back, dim3(l5_grid), dim3(HID), 0, s, mo->dy, mo->z[3], n, mo->P, mo->p5, mo->dzb[1],
-                     mo->dzT[1], ldT);
-  hipLaunchKernelGGL(k_sum_rows, dim3((L5_N + 63) / 64, std::max(1, std::min(16, l5_grid / 4))), dim3(256), 0, s,
-                     mo->p5, l5_grid, (long long)L5_LD, L5_N, mo->G + OFF_B4);
-  // hidden layers from the top: dz of layer l + 1 in dzb[cur] (BF16,
-  // row-major) and dzT[cur] (its transpose)
-  const long long offw[3] = {OFF_W2, OFF_W3, OFF_W4}, offb[3] = {OFF_B2, OFF_B3, OFF_B4};
-  int cur = 1;
-  for (int l = 3; l >= 1; --l) {
-    // dW_{l+1} = a_l^T dz: both operands transposed so that the batch (the
-    // sum) is their contiguous index, split over the rows into partial
-    // products, then summed
-    const int splits = gemm(s, mo->aT[l - 1], ldT, mo->dzT[cur], ldT, HID, HID, n, EPI_SPLIT, nullptr, 0,
-                            mo->wpart, HID, nullptr, 0, split_for(n));
-    hipLaunchKernelGGL(k_sum_rows, dim3(HID * HID / 64, 1), dim3(256), 0, s, mo->wpart, splits,
-                       (long long)HID * HID, HID * HID, mo->G + offw[l - 1]);
-    // dz_l = (dz W_{l+1}^T) * silu'(z_l) (B(k, j) = W(in=j, out=k), row-major
-    // copy) with its per-row-tile column sums: for l >= 2 dz_l goes out in
-    // BF16 (both layouts) and the sums make db_l; dz_1 (FP32) never leaves
-    // the tile: its sums xf^T dz_1 and sum dz_1 are the gradients of W1 and
-    // b1 (contiguous in the parameter vector)
-    const int nrt = (int)gblocks(n, 64), ns = l >= 2 ? 1 : NIN + 1;
-    gemm(s, mo->dzb[cur], HID, wr(mo, l - 1), HID, n, HID, HID, EPI_DSILU, mo->z[l - 1], HID, nullptr, 0,
-         l >= 2 ? mo->dzb[cur ^ 1] : nullptr, HID, 1, mo->cpart, l >= 2 ? mo->dzT[cur ^ 1] : nullptr, ldT,
-         l >= 2 ? nullptr : mo->xf);
-    hipLaunchKernelGGL(k_sum_rows, dim3(ns * HID / 64, std::max(1, std::min(16, nrt / 4))), dim3(256), 0, s,
-                       mo->cpart, nrt, (long long)ns * HID, ns * HID, mo->G + (l >= 2 ? offb[l - 2] : OFF_W1));
-    cur ^= 1;
-  }
+  // splits of at least two steps of 64 rows, two blocks per CU for large batches
+  int splits = std::min(WG_SPLITS, std::max(1, n / (2 * WG_K)));
+  const int kchunk = ((n + splits - 1) / splits + WG_K - 1) / WG_K * WG_K;
+  splits = (n + kchunk - 1) / kchunk;
+  WGrad g{{mo->a[0], mo->a[1], mo->a[2]}, {mo->dz[0], mo->dz[1], mo->dz[2]}, mo->wpart, n, kchunk,
+          3 * WG_TILES * splits};
+  // (whole groups of WG_TILES per XCD)
+  hipLaunchKernelGGL(k_weight_grad, dim3(8 * WG_TILES * (unsigned)gblocks(3 * splits, 8)), dim3(256), 0, s, g);
+  hipLaunchKernelGGL(k_grad_reduce, dim3(GR_BLOCKS), dim3(GR_THREADS), 0, s, mo->wpart, splits, mo->part, blocks,
+                     mo->G, grads, mo->scal + S_LOSS, loss);
 }
 
 int check_model(rt_model mo) {
@@ -2113,9 +1999,7 @@ int grad_impl(rt_model mo, int64_t n, int64_t ld, const float *x6, const float *
   e = reserve_acts(mo, n);
   if (e) return e;
   hipStream_t s = (hipStream_t)stream;
-  forward_backward(mo, x6, t5, ld, w, (int)n, huber, s);
-  if (grads) (void)hipMemcpyAsync(grads, mo->G, sizeof(float) * NPARAM, hipMemcpyDeviceToDevice, s);
-  if (loss) (void)hipMemcpyAsync(loss, mo->scal + S_LOSS, sizeof(float), hipMemcpyDeviceToDevice, s);
+  forward_backward(mo, x6, t5, ld, w, (int)n, huber, grads, loss, s);
   return launch_err("gradient launch");
 }
 
