@@ -91,7 +91,7 @@ struct Table {
   int *order;   // integrator queue: slots sorted hardest first
   int *key0;    // sort key of each slot
   unsigned int *ctr;
-  unsigned int *bh;  // sort: NBIN x SORT_BLOCKS counts, key-major, then their offsets
+  unsigned int *bh;  // sort: NBIN x SORT_BLOCKS counts, key-major, then their sums up to each block
   long long cap;  // capacity of one segment; segment s starts at s * cap
 };
 
@@ -369,46 +369,44 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_hist(Table T) {
   for (int i = threadIdx.x; i < NBIN; i += blockDim.x) T.bh[i * SORT_BLOCKS + blockIdx.x] = lh[i];
 }
 
-// pass 2: exclusive scan of bh in place by one block of SORT_THREADS threads,
-// each summing a run of E consecutive entries. A small block: it starts on a
-// CU that integrator waves of another stream still occupy, instead of waiting
-// for a whole CU to drain.
-__global__ void __launch_bounds__(SORT_THREADS) k_sort_scan(Table T) {
-  constexpr int E = NBIN * SORT_BLOCKS / SORT_THREADS, NW = SORT_THREADS / 64;
-  static_assert(E % 4 == 0, "runs are read as uint4");
-  __shared__ unsigned int ws[NW];
-  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
-  uint4 *p = (uint4 *)(T.bh + t * E);  // the table is 256-byte aligned
-  unsigned int sum = 0;
-#pragma unroll 8
-  for (int i = 0; i < E / 4; ++i) { const uint4 c = p[i]; sum += c.x + c.y + c.z + c.w; }
-  // inclusive scan of the 64 lane sums, then across the waves
-  unsigned int inc = sum;
+// inclusive scan over the block's threads (SORT_THREADS of them); ws: one
+// entry per wave
+__device__ __forceinline__ unsigned int block_scan(unsigned int v, unsigned int ws[SORT_THREADS / 64]) {
+  const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int d = 1; d < 64; d <<= 1) {
-    const unsigned int u = __shfl_up(inc, d);
-    if (lane >= d) inc += u;
+    const unsigned int u = __shfl_up(v, d);
+    if (lane >= d) v += u;
   }
-  if (lane == 63) ws[w] = inc;
+  if (lane == 63) ws[w] = v;
   __syncthreads();
-  if (t == 0) {
-    unsigned int acc = 0;
-    for (int k = 0; k < NW; ++k) { const unsigned int c = ws[k]; ws[k] = acc; acc += c; }
-  }
-  __syncthreads();
-  unsigned int acc = ws[w] + inc - sum;
-#pragma unroll 8
-  for (int i = 0; i < E / 4; ++i) {
-    const uint4 c = p[i];
-    uint4 o;
-    o.x = acc; acc += c.x;
-    o.y = acc; acc += c.y;
-    o.z = acc; acc += c.z;
-    o.w = acc; acc += c.w;
-    p[i] = o;
-  }
+  for (int k = 0; k < w; ++k) v += ws[k];
+  return v;
 }
 
-// pass 3: place the block's range tile by tile. The keys of one tile are
+// pass 2: inclusive scan over the blocks of each key's counts, in place, one
+// block per key; pass 3 adds the keys before. (As one block over the whole
+// table it was a serial chain of 25 us in every launch of the pipeline; this
+// takes 4.) Small blocks: they start on CUs that integrator waves of another
+// stream still occupy, instead of waiting for a whole CU to drain.
+__global__ void __launch_bounds__(SORT_THREADS) k_sort_scan(Table T) {
+  static_assert(SORT_BLOCKS == 4 * SORT_THREADS, "four counts per thread");
+  __shared__ unsigned int ws[SORT_THREADS / 64];
+  uint4 *p = (uint4 *)(T.bh + (size_t)blockIdx.x * SORT_BLOCKS) + threadIdx.x;  // the table is 256-byte aligned
+  uint4 c = *p;
+  c.y += c.x;
+  c.z += c.y;
+  c.w += c.z;
+  const unsigned int before = block_scan(c.w, ws) - c.w;
+  c.x += before;
+  c.y += before;
+  c.z += before;
+  c.w += before;
+  *p = c;
+}
+
+// pass 3: place the block's range tile by tile. Each key's first place is the
+// count of all smaller keys and of its own in the blocks before, from the
+// scanned table's last column and the one before the block's. The keys of one tile are
 // ranked among equal keys of their wave with ballots; a per-key scan over the
 // tile's (item, wave) groups, added to the block's running offset of the
 // key, orders the groups. Every slot lands after the slots of its key that
@@ -420,7 +418,16 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_scatter(Table T) {
   const SegMap m = seg_map(T);
   unsigned int lo, hi;
   sort_range(m.off[NSEG], blockIdx.x, lo, hi);
-  for (int i = threadIdx.x; i < NBIN; i += blockDim.x) run[i] = T.bh[i * SORT_BLOCKS + blockIdx.x];
+  if (lo >= hi) return;
+  {
+    __shared__ unsigned int ws[NW];
+    const int t = threadIdx.x;
+    const unsigned int *bh = T.bh + (size_t)t * SORT_BLOCKS;
+    const unsigned int total = t < NBIN ? bh[SORT_BLOCKS - 1] : 0;
+    const unsigned int own = t < NBIN && blockIdx.x > 0 ? bh[blockIdx.x - 1] : 0;
+    const unsigned int sum = block_scan(total, ws);
+    if (t < NBIN) run[t] = sum - total + own;
+  }
   const int w = threadIdx.x >> 6;
   const unsigned long long lt = lanemask_lt();
   for (unsigned int base = lo; base < hi; base += SORT_ITEMS * SORT_THREADS) {
@@ -2102,7 +2109,7 @@ unsigned int transit_grid(const OptsP &o, int block, bool fres = false) {
 void run_transit(const CloakP &c, const OptsP &o, const Table &T, int block, int refill,
                  unsigned int grid, hipStream_t s, bool profile, bool fres = false) {
   hipLaunchKernelGGL(k_sort_hist, dim3(SORT_BLOCKS), dim3(SORT_THREADS), 0, s, T);
-  hipLaunchKernelGGL(k_sort_scan, dim3(1), dim3(SORT_THREADS), 0, s, T);
+  hipLaunchKernelGGL(k_sort_scan, dim3(NBIN), dim3(SORT_THREADS), 0, s, T);
   hipLaunchKernelGGL(k_sort_scatter, dim3(SORT_BLOCKS), dim3(SORT_THREADS), 0, s, T);
   ProfEvent pe;
   bool on = false;
