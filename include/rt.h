@@ -27,11 +27,11 @@
  *    rt_render and rt_render_multi keep up to four workspaces, one per
  *    stream they are called on (a fifth stream takes the one used longest
  *    ago): renders issued on several streams run side by side, at one
- *    workspace's memory per stream. A call waits on the host for its
- *    workspace's previous use before it copies its camera records. Renders are processed in
- *    chunks of camera samples (2^26 unless max_chunk says otherwise, at most
- *    2^28), with a workspace of ~0.5 KB per sample of a chunk (~31 GB for a
- *    4096 x 4096 x 4 spp view).
+ *    workspace's memory per stream. (A render of more than 64 cameras waits
+ *    on the host for its workspace's previous use before it copies its camera
+ *    records.) Renders are processed in chunks of camera samples (2^26 unless
+ *    max_chunk says otherwise, at most 2^28), with a workspace of ~0.5 KB per
+ *    sample of a chunk (~31 GB for a 4096 x 4096 x 4 spp view).
  */
 #ifndef RT_H
 #define RT_H

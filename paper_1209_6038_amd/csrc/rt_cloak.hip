@@ -225,6 +225,24 @@ __device__ __forceinline__ void put_slot(const Table &T, int s, const double x[3
 // ---------------------------------------------------------------------------
 // kernels
 // ---------------------------------------------------------------------------
+// camera records and colour table of a render by value, PUT_CAMS per launch: a
+// copy from the host's own memory would have to be waited for, 45 us during
+// which the GPU is idle at the start of every render
+constexpr int PUT_CAMS = 8, PUT_LAUNCHES = 8, TABLE_LEN = 39;
+struct JobRecords {
+  CamP cams[PUT_CAMS];
+  float table[TABLE_LEN];
+  int first, n;
+};
+__global__ void k_put_records(JobRecords j, CamP *__restrict__ cams, float *__restrict__ table) {
+  static_assert(sizeof(CamP) % 8 == 0, "copied as 8-byte words");
+  constexpr int W = sizeof(CamP) / 8;
+  const unsigned long long *src = reinterpret_cast<const unsigned long long *>(j.cams);
+  unsigned long long *dst = reinterpret_cast<unsigned long long *>(cams + j.first);
+  for (int e = threadIdx.x; e < j.n * W; e += blockDim.x) dst[e] = src[e];
+  if ((int)threadIdx.x < TABLE_LEN) table[threadIdx.x] = j.table[threadIdx.x];
+}
+
 __global__ void k_zero(unsigned int *p, int n) {
   int i = blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = 0u;
@@ -2293,12 +2311,30 @@ int ws_reserve_for(Workspace &ws, const RenderJob &J) {
   return ws_reserve(ws, J.chunk, J.chunk * J.R.ncl * J.R.npol, (int)J.cams.size());
 }
 
-// copy the job's camera records and colour table into the workspace
-// (synchronous: the host vectors may be freed afterwards)
+// The job's camera records and colour table into the workspace, in stream
+// order: by value for up to PUT_CAMS x PUT_LAUNCHES cameras (3 us a launch),
+// else as copies that are waited for (45 us; the host vectors may be freed
+// afterwards). Not within a capture by the caller, which neither was ever
+// part of: the workspace belongs to the library.
 int upload_job(const RenderJob &J, const Workspace &ws, hipStream_t s) {
-  if (hipMemcpyAsync(ws.cams, J.cams.data(), sizeof(CamP) * J.cams.size(), hipMemcpyHostToDevice, s) !=
-          hipSuccess ||
-      hipMemcpyAsync(ws.table, J.table, sizeof(float) * 39, hipMemcpyHostToDevice, s) != hipSuccess ||
+  hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
+    (void)hipGetLastError();
+    return fail(RT_E_DEVICE, "upload of camera records failed");
+  }
+  const int n = (int)J.cams.size();
+  if (n <= PUT_CAMS * PUT_LAUNCHES) {
+    JobRecords r{};
+    std::copy(J.table, J.table + TABLE_LEN, r.table);
+    for (r.first = 0; r.first < n; r.first += PUT_CAMS) {
+      r.n = std::min(PUT_CAMS, n - r.first);
+      std::copy(J.cams.begin() + r.first, J.cams.begin() + r.first + r.n, r.cams);
+      hipLaunchKernelGGL(k_put_records, dim3(1), dim3(256), 0, s, r, ws.cams, ws.table);
+    }
+    return launch_err("upload of camera records");
+  }
+  if (hipMemcpyAsync(ws.cams, J.cams.data(), sizeof(CamP) * n, hipMemcpyHostToDevice, s) != hipSuccess ||
+      hipMemcpyAsync(ws.table, J.table, sizeof(float) * TABLE_LEN, hipMemcpyHostToDevice, s) != hipSuccess ||
       hipStreamSynchronize(s) != hipSuccess)
     return fail(RT_E_DEVICE, "upload of camera records failed");
   return RT_OK;
@@ -2860,6 +2896,8 @@ int rt_render_plan_create(const rt_cloak *cloaks, int32_t n_cloaks, const rt_tra
   if (!e && hipStreamCreateWithFlags(&cs, hipStreamNonBlocking) != hipSuccess)
     e = fail(RT_E_DEVICE, "stream creation failed");
   if (!e) e = upload_job(p->J, p->ws, cs);
+  // launches may come on any stream
+  if (!e && hipStreamSynchronize(cs) != hipSuccess) e = fail(RT_E_DEVICE, "upload of camera records failed");
   if (!e) {
     p->rgb = rgb;
     if (hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal) != hipSuccess) {
