@@ -226,7 +226,7 @@ __device__ __forceinline__ void put_slot(const Table &T, int s, const double x[3
 // kernels
 // ---------------------------------------------------------------------------
 // camera records and colour table of a render by value, PUT_CAMS per launch: a
-// copy from the host's own memory would have to be waited for, 45 us during
+// copy from the host's own memory would have to be waited for, some 20 us during
 // which the GPU is idle at the start of every render
 constexpr int PUT_CAMS = 8, PUT_LAUNCHES = 8, TABLE_LEN = 39;
 struct JobRecords {
@@ -2313,7 +2313,7 @@ int ws_reserve_for(Workspace &ws, const RenderJob &J) {
 
 // The job's camera records and colour table into the workspace, in stream
 // order: by value for up to PUT_CAMS x PUT_LAUNCHES cameras (3 us a launch),
-// else as copies that are waited for (45 us; the host vectors may be freed
+// else as copies that are waited for (20 us; the host vectors may be freed
 // afterwards). Not within a capture by the caller, which neither was ever
 // part of: the workspace belongs to the library.
 int upload_job(const RenderJob &J, const Workspace &ws, hipStream_t s) {
