@@ -322,15 +322,6 @@ __device__ __forceinline__ void features(const float *__restrict__ x6, long long
   }
 }
 
-// standardized outputs (n x 5) -> SoA targets (5 x ld)
-__global__ void k_destd(const float *__restrict__ y, int n, long long ld, const float *__restrict__ sc,
-                        float *__restrict__ t) {
-  const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= (long long)n * NOUT) return;
-  const int row = (int)(i / NOUT), o = (int)(i - (long long)row * NOUT);
-  t[o * ld + row] = fmaf(y[i], sc[S_OSTD + o], sc[S_OMEAN + o]);
-}
-
 __global__ void k_fill(float *p, long long n, float v) {
   const long long i = (long long)blockIdx.x * blockDim.x + threadIdx.x;
   if (i < n) p[i] = v;
@@ -754,23 +745,48 @@ __global__ void __launch_bounds__(256) k_gate_idx(const float *__restrict__ x6, 
 // accumulators per lane. Layer 1 (FP32) fills the tile; layer 5 (FP32)
 // reduces the layer-4 accumulators over each lane's 16 units, across the 4
 // lane groups of a wave, then across the 4 waves through LDS, and the block
-// writes the standardized outputs (n x 5).
+// writes the standardized outputs (n x 5) or the targets themselves.
+//
+// The vector instructions bound it (the 1024 SiLUs of an entry above all: 400
+// us of issue for 2^20 entries, at the 2.2 GHz it runs at), but one wave's SiLUs
+// and products (matrix cores: 165 us) followed each other, and the two waves of
+// a SIMD did not make up for it. So the tile is worked on in two halves of 64
+// rows, one layer step apart: every step multiplies one half and applies the
+// previous step's SiLUs to the other in the same instruction stream, 16 matrix
+// instructions and the SiLUs of 8 values per lane for each 32 inputs. Weights
+// come FDEPTH such groups ahead, across steps (1 to 3: 552, 540, 568 us).
+// 2^20 entries: 634 -> 540 us, 18 of them for the targets written from here
+// instead of by a launch of their own, 40 for the weights in operand order.
 // ---------------------------------------------------------------------------
-constexpr int FR = 128, ALD = HID + 8;
+constexpr int FR = 128, FH = FR / 2, ALD = HID + 8, FDEPTH = 2;
 
 // With idx != NULL, row r of the network is entry idx[r] for r < *count
-// (a compacted subset); otherwise row r is entry r, r < n.
+// (a compacted subset); otherwise row r is entry r, r < n. With t != NULL the
+// outputs go there as targets (5 x ldt), else to yout.
 __global__ void __launch_bounds__(256, 2) k_mlp_fused(const float *__restrict__ x6, long long ld, int n,
                                                       const int *__restrict__ idx, const unsigned int *count,
                                                       const float *__restrict__ P, const bf16 *__restrict__ Wt,
                                                       const float *__restrict__ sc, JobP jp,
-                                                      float *__restrict__ yout) {
+                                                      float *__restrict__ yout, float *__restrict__ t,
+                                                      long long ldt) {
   __shared__ __attribute__((aligned(16))) bf16 act[FR * ALD];
   __shared__ float xn[FR * NIN];
   const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+  const int q = lane >> 4, c16 = lane & 15, ub = 64 * w;
   const long long row0 = (long long)blockIdx.x * FR;
   if (idx) n = (int)*count;  // block-uniform
   if (row0 >= n) return;
+  // weights of group g = (step, 32 inputs): ring of FDEPTH + 1
+  constexpr int KS = HID / 32;
+  bf16x8 wf[FDEPTH + 1][4];
+  const auto load_group = [&](int g) {
+    const bf16 *W = Wt + (g / (2 * KS)) * HID * HID + (4 * w * KS + g % KS) * 512 + 8 * lane;
+#pragma unroll
+    for (int ti = 0; ti < 4; ++ti)
+      wf[g % (FDEPTH + 1)][ti] = *reinterpret_cast<const bf16x8 *>(W + ti * KS * 512);
+  };
+#pragma unroll
+  for (int g = 0; g < FDEPTH; ++g) load_group(g);
   // standardized input features of the tile (rows past n read as zeros)
   if (tid < FR) {
     const long long i = row0 + tid;
@@ -784,118 +800,146 @@ __global__ void __launch_bounds__(256, 2) k_mlp_fused(const float *__restrict__ 
     for (int k = 0; k < NIN; ++k) xn[tid * NIN + k] = f[k];
   }
   __syncthreads();
-  {  // layer 1 (FP32): thread = pair of hidden units x half of the rows
-    const int u = 2 * (tid & 127), rb = (tid >> 7) * (FR / 2);
-    float w0[NIN], w1[NIN];
+  // layer 1 (FP32): thread = pair of hidden units x half of a half's rows
+  float w0[NIN], w1[NIN], b0, b1;
+  {
+    const int u = 2 * (tid & 127);
 #pragma unroll
     for (int k = 0; k < NIN; ++k) {
       w0[k] = P[OFF_W1 + k * HID + u];
       w1[k] = P[OFF_W1 + k * HID + u + 1];
     }
-    const float b0 = P[OFF_B1 + u], b1 = P[OFF_B1 + u + 1];
-    for (int r = rb; r < rb + FR / 2; ++r) {
-      float z0 = b0, z1 = b1;
-#pragma unroll
-      for (int k = 0; k < NIN; ++k) {
-        z0 = fmaf(xn[r * NIN + k], w0[k], z0);
-        z1 = fmaf(xn[r * NIN + k], w1[k], z1);
-      }
-      bf16x2 pr;
-      pr[0] = (bf16)silu_f(z0);
-      pr[1] = (bf16)silu_f(z1);
-      *reinterpret_cast<bf16x2 *>(&act[r * ALD + u]) = pr;
-    }
+    b0 = P[OFF_B1 + u];
+    b1 = P[OFF_B1 + u + 1];
   }
+  const auto layer1 = [&](int r) {
+    float z0 = b0, z1 = b1;
+#pragma unroll
+    for (int k = 0; k < NIN; ++k) {
+      z0 = fmaf(xn[r * NIN + k], w0[k], z0);
+      z1 = fmaf(xn[r * NIN + k], w1[k], z1);
+    }
+    bf16x2 pr;
+    pr[0] = (bf16)silu_f(z0);
+    pr[1] = (bf16)silu_f(z1);
+    *reinterpret_cast<bf16x2 *>(&act[r * ALD + 2 * (tid & 127)]) = pr;
+  };
+  const int r1 = (tid >> 7) * (FH / 2);
+#pragma unroll 4
+  for (int j = 0; j < FH / 2; ++j) layer1(r1 + j);
   __syncthreads();
-  const int q = lane >> 4, c16 = lane & 15, ub = 64 * w;
-  const long long offb[3] = {OFF_B2, OFF_B3, OFF_B4};
-  f32x4 acc[4][8];  // [unit tile][row tile]
-  for (int l = 0; l < 3; ++l) {
-    const bf16 *W = Wt + (long long)l * HID * HID;
+  f32x4 acc[2][4][4];  // [half][unit tile][row tile]
+  // biases of the elementwise steps: 4 consecutive units per unit tile
+  f32x4 bias[4];
+  const auto load_bias = [&](long long off) {
 #pragma unroll
     for (int ti = 0; ti < 4; ++ti)
 #pragma unroll
-      for (int tj = 0; tj < 8; ++tj) acc[ti][tj] = f32x4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 4
-    for (int k0 = 0; k0 < HID; k0 += 32) {
-      bf16x8 aop[4];
+      for (int r = 0; r < 4; ++r) bias[ti][r] = P[off + ub + 16 * ti + 4 * q + r];
+  };
+  // SiLU of unit tile ti, row tile tj of a half into the tile
+  const auto silu_tile = [&](int h, int ti, int tj) {
+    bf16x4 pk;
 #pragma unroll
-      for (int ti = 0; ti < 4; ++ti)
-        aop[ti] = *reinterpret_cast<const bf16x8 *>(W + ((4 * w + ti) * (HID / 32) + k0 / 32) * 512 + 8 * lane);
+    for (int r = 0; r < 4; ++r) pk[r] = (bf16)silu_f(acc[h][ti][tj][r] + bias[ti][r]);
+    *reinterpret_cast<bf16x4 *>(&act[(h * FH + 16 * tj + c16) * ALD + ub + 16 * ti + 4 * q]) = pk;
+  };
+  float s5[4][NOUT];  // layer 5: partial sums over this lane's 16 units for each of a half's rows
+  const auto out_tile = [&](int h, int ti, int tj, const float w5[4][NOUT]) {
 #pragma unroll
-      for (int tj = 0; tj < 8; ++tj) {
-        const bf16x8 bop = *reinterpret_cast<const bf16x8 *>(&act[(16 * tj + c16) * ALD + k0 + 8 * q]);
+    for (int r = 0; r < 4; ++r) {
+      const float a4 = silu_f(acc[h][ti][tj][r] + bias[ti][r]);
 #pragma unroll
-        for (int ti = 0; ti < 4; ++ti)
-          acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(aop[ti], bop, acc[ti][tj], 0, 0, 0);
+      for (int o = 0; o < NOUT; ++o) s5[tj][o] = fmaf(a4, w5[r][o], s5[tj][o]);
+    }
+  };
+  const auto load_w5 = [&](int ti, float w5[4][NOUT]) {
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+#pragma unroll
+      for (int o = 0; o < NOUT; ++o) w5[r][o] = P[OFF_W5 + (ub + 16 * ti + 4 * q + r) * NOUT + o];
+  };
+  float *red = reinterpret_cast<float *>(act);  // [half][wave][FH][NOUT], once the tile is not read any more
+  const auto reduce_half = [&](int h) {
+#pragma unroll
+    for (int tj = 0; tj < 4; ++tj) {
+#pragma unroll
+      for (int o = 0; o < NOUT; ++o) {
+        s5[tj][o] += __shfl_xor(s5[tj][o], 16);
+        s5[tj][o] += __shfl_xor(s5[tj][o], 32);
+      }
+      if (q == 0) {
+#pragma unroll
+        for (int o = 0; o < NOUT; ++o) red[((h * 4 + w) * FH + 16 * tj + c16) * NOUT + o] = s5[tj][o];
       }
     }
-    __syncthreads();  // every wave has read the layer's input tile
-    if (l < 2) {
+  };
+  // step st multiplies half st & 1 by layer 2 + st / 2
 #pragma unroll
-      for (int ti = 0; ti < 4; ++ti) {
-        const int u0 = ub + 16 * ti + 4 * q;  // this lane's 4 consecutive units
-        float bias[4];
+  for (int st = 0; st < 6; ++st) {
+    const int h = st & 1, o = 1 - h;
+    if (st >= 1) load_bias((st - 1) / 2 == 0 ? OFF_B2 : (st - 1) / 2 == 1 ? OFF_B3 : OFF_B4);
+    if (st == 5) {
 #pragma unroll
-        for (int r = 0; r < 4; ++r) bias[r] = P[offb[l] + u0 + r];
+      for (int tj = 0; tj < 4; ++tj)
 #pragma unroll
-        for (int tj = 0; tj < 8; ++tj) {
-          bf16x4 pk;
+        for (int k = 0; k < NOUT; ++k) s5[tj][k] = 0.0f;
+    }
+    float w5[4][NOUT];
 #pragma unroll
-          for (int r = 0; r < 4; ++r) pk[r] = (bf16)silu_f(acc[ti][tj][r] + bias[r]);
-          *reinterpret_cast<bf16x4 *>(&act[(16 * tj + c16) * ALD + u0]) = pk;
-        }
+    for (int ks = 0; ks < KS; ++ks) {
+      const int g = st * KS + ks;
+      if (g + FDEPTH < 6 * KS) load_group(g + FDEPTH);
+      bf16x8 bop[4];
+#pragma unroll
+      for (int tj = 0; tj < 4; ++tj)
+        bop[tj] = *reinterpret_cast<const bf16x8 *>(&act[(h * FH + 16 * tj + c16) * ALD + 32 * ks + 8 * q]);
+#pragma unroll
+      for (int tj = 0; tj < 4; ++tj)
+#pragma unroll
+        for (int ti = 0; ti < 4; ++ti)
+          acc[h][ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(
+              wf[g % (FDEPTH + 1)][ti], bop[tj], ks == 0 ? f32x4{0.f, 0.f, 0.f, 0.f} : acc[h][ti][tj], 0, 0, 0);
+      if (st == 0) {
+#pragma unroll
+        for (int j = 0; j < FH / 2 / KS; ++j) layer1(FH + r1 + ks * (FH / 2 / KS) + j);
+      } else if (st < 5) {
+        silu_tile(o, ks >> 1, 2 * (ks & 1));
+        silu_tile(o, ks >> 1, 2 * (ks & 1) + 1);
+      } else {
+        if (!(ks & 1)) load_w5(ks >> 1, w5);
+        out_tile(o, ks >> 1, 2 * (ks & 1), w5);
+        out_tile(o, ks >> 1, 2 * (ks & 1) + 1, w5);
       }
-      __syncthreads();
-    } else {
-      // layer 5 (FP32) on a4 = silu(z4): partial sums over this lane's 16
-      // units for each of its 8 rows, then over the 4 lane groups
-      float s5[8][NOUT];
+    }
+    __syncthreads();  // the other half's tile is written, this half's read
+  }
+  reduce_half(0);
+  load_bias(OFF_B4);
 #pragma unroll
-      for (int tj = 0; tj < 8; ++tj)
+  for (int tj = 0; tj < 4; ++tj)
 #pragma unroll
-        for (int o = 0; o < NOUT; ++o) s5[tj][o] = 0.0f;
+    for (int k = 0; k < NOUT; ++k) s5[tj][k] = 0.0f;
 #pragma unroll
-      for (int ti = 0; ti < 4; ++ti) {
-        const int u0 = ub + 16 * ti + 4 * q;
-        float bias[4], w5[4][NOUT];
+  for (int ti = 0; ti < 4; ++ti) {
+    float w5[4][NOUT];
+    load_w5(ti, w5);
 #pragma unroll
-        for (int r = 0; r < 4; ++r) {
-          bias[r] = P[offb[l] + u0 + r];
+    for (int tj = 0; tj < 4; ++tj) out_tile(1, ti, tj, w5);
+  }
+  reduce_half(1);
+  __syncthreads();
+  if (tid < FR) {
+    const long long i = row0 + tid;
+    const float *rd = red + (tid / FH * 4 * FH + tid % FH) * NOUT;
+    if (i < n) {
 #pragma unroll
-          for (int o = 0; o < NOUT; ++o) w5[r][o] = P[OFF_W5 + (u0 + r) * NOUT + o];
-        }
-#pragma unroll
-        for (int tj = 0; tj < 8; ++tj)
-#pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            const float a4 = silu_f(acc[ti][tj][r] + bias[r]);
-#pragma unroll
-            for (int o = 0; o < NOUT; ++o) s5[tj][o] = fmaf(a4, w5[r][o], s5[tj][o]);
-          }
-      }
-      float *red = reinterpret_cast<float *>(act);  // [4 waves][FR][NOUT]
-#pragma unroll
-      for (int tj = 0; tj < 8; ++tj) {
-#pragma unroll
-        for (int o = 0; o < NOUT; ++o) {
-          s5[tj][o] += __shfl_xor(s5[tj][o], 16);
-          s5[tj][o] += __shfl_xor(s5[tj][o], 32);
-        }
-        if (q == 0) {
-#pragma unroll
-          for (int o = 0; o < NOUT; ++o) red[(w * FR + 16 * tj + c16) * NOUT + o] = s5[tj][o];
-        }
-      }
-      __syncthreads();
-      if (tid < FR) {
-        const long long i = row0 + tid;
-        if (i < n) {
-#pragma unroll
-          for (int o = 0; o < NOUT; ++o)
-            yout[i * NOUT + o] = P[OFF_B5 + o] + ((red[(0 * FR + tid) * NOUT + o] + red[(1 * FR + tid) * NOUT + o]) +
-                                                  (red[(2 * FR + tid) * NOUT + o] + red[(3 * FR + tid) * NOUT + o]));
-        }
+      for (int o = 0; o < NOUT; ++o) {
+        const float y = P[OFF_B5 + o] + ((rd[o] + rd[FH * NOUT + o]) + (rd[2 * FH * NOUT + o] + rd[3 * FH * NOUT + o]));
+        if (t)
+          t[o * ldt + i] = fmaf(y, sc[S_OSTD + o], sc[S_OMEAN + o]);
+        else
+          yout[i * NOUT + o] = y;
       }
     }
   }
@@ -1676,10 +1720,11 @@ JobP job_for(rt_model mo, const rt_cloak_desc *d) {
               std::isfinite(d->z1) ? (float)d->z1 : INFINITY};
 }
 
-// standardized outputs of n rows into mo->yinf (fused kernel)
-void infer_outputs(rt_model mo, const float *x, long long ld, int n, hipStream_t s) {
+// outputs of n rows (fused kernel): targets into t (5 x ldt), or where t is
+// NULL standardized into mo->yinf
+void infer_outputs(rt_model mo, const float *x, long long ld, int n, float *t, long long ldt, hipStream_t s) {
   hipLaunchKernelGGL(k_mlp_fused, dim3(gblocks(n, FR)), dim3(256), 0, s, x, ld, n, nullptr, nullptr, mo->P, mo->Pb,
-                     mo->scal, job_for(mo, nullptr), mo->yinf);
+                     mo->scal, job_for(mo, nullptr), mo->yinf, t, ldt);
 }
 
 // BF16 weights of W2 (l = 0), W3 (1), W4 (2) for the backward products (mo->Pb: forward)
@@ -1812,7 +1857,7 @@ int surrogate_predict_gated(rt_model mo, const rt_cloak_desc &d, int64_t n, int6
       hipLaunchKernelGGL(k_pregate, dim3(gblocks(rows, 256)), dim3(256), 0, s, x, (long long)ld, rows, m->map, gp, jp,
                          m == mo ? 0 : 1, fallback + off, m->idx, m->count);
       hipLaunchKernelGGL(k_mlp_fused, dim3(gblocks(rows, FR)), dim3(256), 0, s, x, (long long)ld, rows, m->idx,
-                         m->count, m->P, m->Pb, m->scal, jp, m->yinf);
+                         m->count, m->P, m->Pb, m->scal, jp, m->yinf, nullptr, 0LL);
       hipLaunchKernelGGL(k_gate_idx, dim3(gblocks(rows, 256)), dim3(256), 0, s, x, (long long)ld, m->idx, m->count,
                          m->yinf, m->scal, m->map, gp, jp, y5 + off, fallback + off, status + off);
     }
@@ -2075,12 +2120,7 @@ int rt_surrogate_forward(rt_model mo, int64_t n, int64_t ld, const float *x6, fl
   if (!e) e = check_rows(n, ld, x6);
   if (e) return e;
   if (!t5) return fail(RT_E_INVALID, "t5 is required");
-  e = reserve_yinf(mo, n);
-  if (e) return e;
-  hipStream_t s = (hipStream_t)stream;
-  infer_outputs(mo, x6, ld, (int)n, s);
-  hipLaunchKernelGGL(k_destd, dim3(gblocks(n * NOUT, 256)), dim3(256), 0, s, mo->yinf, (int)n, (long long)ld,
-                     mo->scal, t5);
+  infer_outputs(mo, x6, ld, (int)n, t5, ld, (hipStream_t)stream);
   return launch_err("forward launch");
 }
 
@@ -2133,7 +2173,7 @@ int rt_surrogate_calibrate(rt_model mo, const rt_cloak *cloaks, int32_t n_cloaks
   e = reserve_yinf(mo, n);
   if (e) return e;
   hipStream_t s = (hipStream_t)stream;
-  infer_outputs(mo, x6, ld, (int)n, s);
+  infer_outputs(mo, x6, ld, (int)n, nullptr, 0, s);
   hipLaunchKernelGGL(k_fill_u32, dim3(gblocks(2LL * NCELLS, 256)), dim3(256), 0, s, mo->cal, 2LL * NCELLS);
   hipLaunchKernelGGL(k_calib, dim3(gblocks(n, 256)), dim3(256), 0, s, x6, (long long)ld, (int)n, mo->yinf, mo->scal,
                      y5_exact, status_exact, hres_exact, (float)gate->unresolved,
