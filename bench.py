@@ -873,7 +873,7 @@ def orbit_headline(args, log):
         torch.cuda.synchronize()
         log(f"orbit launch shape: block {opts['block']}, refill period {opts['refill_period']} "
             f"({tuned_ms:.1f} ms per launch group)")
-    shape = (opts.get("block") or 256, opts.get("refill_period") or 2)
+    shape = (opts.get("block") or 256, opts.get("refill_period") or 4)
     # images per launch group, each a dense [cloak][frame][branch][h][w][3] block
     out = torch.empty((len(groups), 2, fpl, 2, 4096, 4096, 3), dtype=torch.float32, device=dev)
     # consecutive launch groups alternate between streams: the library keeps
@@ -1115,7 +1115,7 @@ def _plan_record(args, log, cams, name, desc, cpu_stride):
     tuned_ms = None
     if not (args.block or args.refill):
         opts, tuned_ms = rt.autotune_render(cloaks, opts, room, cams, 3)
-    opts["block"], opts["refill_period"] = opts.get("block") or 256, opts.get("refill_period") or 2
+    opts["block"], opts["refill_period"] = opts.get("block") or 256, opts.get("refill_period") or 4
     nstreams = 3
     plans = [rt.RenderPlan(cloaks, opts, room, cams, 3) for _ in range(nstreams)]
     streams = [torch.cuda.Stream() for _ in range(nstreams)]
