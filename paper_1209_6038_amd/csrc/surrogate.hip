@@ -1003,6 +1003,16 @@ template <int CTRL>
 __device__ __forceinline__ float fold(float v0, float v1, bool upper) {
   return (upper ? v1 : v0) + dpp<CTRL>(upper ? v0 : v1);
 }
+// sums of v0 over lanes l and l ^ 32 in lanes 0..31, of v1 in lanes 32..63;
+// and over lanes l and l ^ 16, v0 in the even rows of 16 lanes and v1 in the odd
+__device__ __forceinline__ float fold32(float v0, float v1) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
+__device__ __forceinline__ float fold16(float v0, float v1) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(v0), __float_as_uint(v1), false, false);
+  return __uint_as_float(r[0]) + __uint_as_float(r[1]);
+}
 struct RowFold {
   bool b3, b2, b1;
   __device__ explicit RowFold(int c16) : b3(c16 & 8), b2(c16 & 4), b1(c16 & 2) {}
@@ -1035,14 +1045,24 @@ __device__ __forceinline__ float pin(float x) {
   return x;
 }
 
-// the block's activation tile to rows row0.. of dst [n][256], 16 bytes per lane
+// the block's activation tile of R rows, the first `rows` of them in the
+// batch, to rows row0.. of dst [n][256], 16 bytes per lane
+template <int R>
 __device__ __forceinline__ void store_tile(const bf16 *act, bf16 *__restrict__ dst, long long row0, int rows,
                                            int tid) {
-  const int c = 8 * (tid & 31);
+  constexpr int STEP = TRAIN_THREADS / 32;
+  const int c = 8 * (tid & 31), r0 = tid >> 5;
   bf16 *d = dst + row0 * HID + c;
-#pragma unroll 2
-  for (int r = tid >> 5; r < rows; r += TRAIN_THREADS / 32)
-    *reinterpret_cast<bf16x8 *>(d + r * HID) = *reinterpret_cast<const bf16x8 *>(&act[r * ALD + c]);
+  if (rows == R) {
+    bf16x8 v[R / STEP];
+#pragma unroll
+    for (int k = 0; k < R / STEP; ++k) v[k] = *reinterpret_cast<const bf16x8 *>(&act[(r0 + k * STEP) * ALD + c]);
+#pragma unroll
+    for (int k = 0; k < R / STEP; ++k) *reinterpret_cast<bf16x8 *>(d + (r0 + k * STEP) * HID) = v[k];
+  } else {
+    for (int r = r0; r < rows; r += STEP)
+      *reinterpret_cast<bf16x8 *>(d + r * HID) = *reinterpret_cast<const bf16x8 *>(&act[r * ALD + c]);
+  }
 }
 
 // One block of 8 waves per CU; R = 16 NT rows per tile. Products are computed
@@ -1054,10 +1074,11 @@ __device__ __forceinline__ void store_tile(const bf16 *act, bf16 *__restrict__ d
 // registers) is loaded during the elementwise phase before it, the thin
 // parameters are in LDS, and inputs and targets of the next 512 rows are
 // fetched, and the inputs' sines and cosines taken, by all threads at once.
-// 65,536 rows: 143 us, of which the matrix products need 21 and the vector
+// 65,536 rows: 127 us, of which the matrix products need 21 and the vector
 // instructions 54 (SiLU and its derivative, 5 exponentials and reciprocals
 // per unit and row); as 4 waves of 64 units with the weights loaded where
-// they are used, 250.
+// they are used, 250; with each operand read from LDS waited for (a product
+// 4400 clocks instead of 2700), 142.
 template <int NT>
 __global__ void __launch_bounds__(TRAIN_THREADS, 2) k_mlp_train(const float *__restrict__ x6, long long ld, int n,
                                                                 const float *__restrict__ P, const bf16 *Wt,
@@ -1118,15 +1139,24 @@ __global__ void __launch_bounds__(TRAIN_THREADS, 2) k_mlp_train(const float *__r
       for (int ti = 0; ti < 2; ++ti)
 #pragma unroll
         for (int tj = 0; tj < NT; ++tj) acc[ti][tj] = f32x4{0.f, 0.f, 0.f, 0.f};
+      // the rows' operands come one group of 32 inputs ahead
+      bf16x8 bop[2][NT];
+      const auto load_rows = [&](int ks) {
 #pragma unroll
-      for (int ks = 0; ks < HID / 32; ++ks)
+        for (int tj = 0; tj < NT; ++tj)
+          bop[ks & 1][tj] = *reinterpret_cast<const bf16x8 *>(&act[(16 * tj + c16) * ALD + 32 * ks + 8 * q]);
+      };
+      load_rows(0);
 #pragma unroll
-        for (int tj = 0; tj < NT; ++tj) {
-          const bf16x8 bop = *reinterpret_cast<const bf16x8 *>(&act[(16 * tj + c16) * ALD + 32 * ks + 8 * q]);
+      for (int ks = 0; ks < HID / 32; ++ks) {
+        if (ks + 1 < HID / 32) load_rows(ks + 1);
+        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+        for (int tj = 0; tj < NT; ++tj)
 #pragma unroll
           for (int ti = 0; ti < 2; ++ti)
-            acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ti][ks], bop, acc[ti][tj], 0, 0, 0);
-        }
+            acc[ti][tj] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(wf[ti][ks], bop[ks & 1][tj], acc[ti][tj], 0, 0, 0);
+      }
     };
     const auto vec = [&](int col) { return *reinterpret_cast<const f32x4 *>(&th[col]); };
     load_weights(Wt);
@@ -1163,7 +1193,7 @@ __global__ void __launch_bounds__(TRAIN_THREADS, 2) k_mlp_train(const float *__r
     }
     __syncthreads();
     const auto hidden = [&](bf16 *a, const bf16 *next, int bias_col, f32x4 (&ds)[2][NT]) {
-      store_tile(act, a, row0, rows, tid);
+      store_tile<R>(act, a, row0, rows, tid);
       product();
       load_weights(next);
       __syncthreads();  // every wave has read the layer's input tile
@@ -1187,7 +1217,7 @@ __global__ void __launch_bounds__(TRAIN_THREADS, 2) k_mlp_train(const float *__r
     };
     hidden(ts.a[0], Wt + HID * HID, PS_B2, ds2);
     hidden(ts.a[1], Wt + 2 * HID * HID, PS_B3, ds3);
-    store_tile(act, ts.a[2], row0, rows, tid);
+    store_tile<R>(act, ts.a[2], row0, rows, tid);
     product();
     {
       // layer 5 (FP32) on a4 = silu(z4): partial sums over this lane's 8
@@ -1216,14 +1246,24 @@ __global__ void __launch_bounds__(TRAIN_THREADS, 2) k_mlp_train(const float *__r
               s5[tj][o] = fmaf(a4, w5[(r * NOUT + o) / 4][(r * NOUT + o) % 4], s5[tj][o]);
           }
       }
-#pragma unroll
-      for (int tj = 0; tj < NT; ++tj)
+      if constexpr (NT == 4) {
+        // fold the 4 row tiles over the 4 lane groups: lane group q ends up
+        // with row tile 2 (q & 1) + (q >> 1)
 #pragma unroll
         for (int o = 0; o < NOUT; ++o) {
-          s5[tj][o] += __shfl_xor(s5[tj][o], 16);
-          s5[tj][o] += __shfl_xor(s5[tj][o], 32);
-          if (q == 0) red[w * RED + (16 * tj + c16) * NOUT + o] = s5[tj][o];
+          const float lo = fold32(s5[0][o], s5[1][o]), hi = fold32(s5[2][o], s5[3][o]);
+          red[w * RED + (16 * (2 * (q & 1) + (q >> 1)) + c16) * NOUT + o] = fold16(lo, hi);
         }
+      } else {
+#pragma unroll
+        for (int tj = 0; tj < NT; ++tj)
+#pragma unroll
+          for (int o = 0; o < NOUT; ++o) {
+            s5[tj][o] += __shfl_xor(s5[tj][o], 16);
+            s5[tj][o] += __shfl_xor(s5[tj][o], 32);
+            if (q == 0) red[w * RED + (16 * tj + c16) * NOUT + o] = s5[tj][o];
+          }
+      }
     }
     load_weights(Wr + 2 * HID * HID);
     __syncthreads();
@@ -1310,7 +1350,7 @@ __global__ void __launch_bounds__(TRAIN_THREADS, 2) k_mlp_train(const float *__r
     __syncthreads();
     // hidden layers: dz_l = (dz_{l+1} W_{l+1}^T) silu'(z_l), db_l = sum dz_l
     const auto hidden_back = [&](bf16 *dz, const bf16 *next, int sums, const f32x4 (&ds)[2][NT]) {
-      store_tile(act, dz, row0, rows, tid);
+      store_tile<R>(act, dz, row0, rows, tid);
       product();
       load_weights(next);
       __syncthreads();
@@ -1339,7 +1379,7 @@ __global__ void __launch_bounds__(TRAIN_THREADS, 2) k_mlp_train(const float *__r
     hidden_back(ts.dz[2], Wr + HID * HID, PS_B3, ds3);
     hidden_back(ts.dz[1], Wr, PS_B2, ds2);
     // dz1 never leaves its registers: dW1 = x^T dz1, db1 = sum dz1
-    store_tile(act, ts.dz[0], row0, rows, tid);
+    store_tile<R>(act, ts.dz[0], row0, rows, tid);
     product();
     {
       float xr[NT][NIN], sz[2], sw[NIN][2];
