@@ -92,24 +92,14 @@ ENTERED = (0, 2, 3, 4, 5)
 # known size (bench.py --copy-probe), per workload and launch shape (block,
 # refill period). Valid only for the integrator source it was measured on;
 # reported as null otherwise, or for a shape that was not measured.
-TRAFFIC = {"source_sha256": "a9a9495366d70c26cce4b56bb0ce7d971ef1e55ade0358be616ac5afc396e310",
+TRAFFIC = {"source_sha256": "ceb053584cfa29b26533f0ee6dafb23027c0f0a3031acff126b7182f62328b78",
            "bytes_per_launch": {
-               "orbit": {(64, 4): 16_367_264_853, (64, 8): 16_602_244_747, (64, 12): 16_738_936_565,
-                         (64, 16): 16_740_058_976, (128, 4): 16_492_896_405, (128, 8): 16_727_920_267,
-                         (128, 12): 16_840_027_520, (128, 16): 16_883_521_525, (256, 4): 16_535_520_341,
-                         (256, 8): 16_765_989_120, (256, 12): 16_876_966_368, (256, 16): 16_928_693_867},
-               "render_1024": {(64, 1): 576_314_856, (64, 2): 578_478_216, (64, 4): 581_150_584,
-                               (64, 8): 585_980_760, (64, 12): 589_803_952, (64, 16): 585_261_208,
-                               (128, 1): 577_334_288, (128, 2): 579_538_424, (128, 4): 582_954_576,
-                               (128, 8): 587_826_800, (128, 12): 591_496_336, (128, 16): 588_082_776,
-                               (256, 1): 582_124_096, (256, 2): 585_049_584, (256, 4): 589_310_288,
-                               (256, 8): 595_968_472, (256, 12): 598_821_816, (256, 16): 594_912_168},
-               "batched": {(64, 1): 2_575_599_168, (64, 2): 2_588_529_816, (64, 4): 2_599_886_416,
-                           (64, 8): 2_611_125_984, (64, 12): 2_614_895_840, (64, 16): 2_602_135_272,
-                           (128, 1): 2_580_383_632, (128, 2): 2_599_642_352, (128, 4): 2_614_251_952,
-                           (128, 8): 2_624_741_968, (128, 12): 2_625_039_016, (128, 16): 2_610_439_112,
-                           (256, 1): 2_593_232_352, (256, 2): 2_614_858_856, (256, 4): 2_633_913_808,
-                           (256, 8): 2_642_026_480, (256, 12): 2_640_291_072, (256, 16): 2_626_358_272}}}
+               "orbit": {(64, 8): 17_285_255_325, (64, 12): 17_354_026_240, (64, 16): 17_395_528_465,
+                         (128, 8): 17_275_913_863, (128, 12): 17_353_971_687, (128, 16): 17_397_513_744,
+                         (256, 8): 17_168_934_619, (256, 12): 17_239_397_595, (256, 16): 17_283_679_932},
+               "render_1024": {(64, 2): 610_335_432, (64, 4): 608_493_981, (64, 8): 618_564_029,
+                               (128, 2): 605_033_310, (128, 4): 604_711_550, (128, 8): 611_586_348,
+                               (256, 2): 608_934_773, (256, 4): 605_956_284, (256, 8): 610_589_576}}}
 
 
 def traffic_for(workload, shape=None):
