@@ -1440,7 +1440,10 @@ struct WGrad {
 };
 
 // 64 rows from k0 of 128 columns, rows past kend as zeros: a buffer load checks
-// its offset against the resource's size, so that the loop has no branches
+// its offset against the resource's size, so that the loop has no branches. All
+// of the offset is in the vector operand: the scalar one is not part of what
+// the instruction promises to check, and rows past kend hold an earlier, larger
+// batch's values.
 typedef unsigned int u32x4 __attribute__((ext_vector_type(4)));
 __device__ __forceinline__ void wg_load(u32x4 v[4], const bf16 *src, int k0, int kend, int col0, int tid) {
   // (all uniform; said so, as the compiler takes vector instructions for parts of it)
@@ -1450,10 +1453,10 @@ __device__ __forceinline__ void wg_load(u32x4 v[4], const bf16 *src, int k0, int
   const unsigned hi = __builtin_amdgcn_readfirstlane((unsigned)(base >> 32));
   const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
       (void *)((unsigned long long)hi << 32 | lo), 0, rows * HID * (int)sizeof(bf16), 0x00027000);
-  const int off = ((tid >> 4) * HID + 8 * (tid & 15)) * (int)sizeof(bf16);
+  const int off = ((tid >> 4) * HID + 8 * (tid & 15) + col0) * (int)sizeof(bf16);
 #pragma unroll
   for (int p = 0; p < 4; ++p)
-    v[p] = __builtin_amdgcn_raw_buffer_load_b128(rs, off, (16 * p * HID + col0) * (int)sizeof(bf16), 0);
+    v[p] = __builtin_amdgcn_raw_buffer_load_b128(rs, off + 16 * p * HID * (int)sizeof(bf16), 0, 0);
 }
 
 __device__ __forceinline__ void wg_store(bf16 *T, const u32x4 v[4], int tid) {
