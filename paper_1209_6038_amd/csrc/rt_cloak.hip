@@ -780,7 +780,9 @@ __device__ __forceinline__ int interface_event(Lane &L, const CloakP &c, const O
   if constexpr (HAM) ham_convert<KIND>(c.a, c.kappa, L.x, L.v, true);  // v -> k
   else if constexpr (SCH == RT_SCHEME_DP45)
     accel<KIND>(c.a, L.x[0], L.x[1], L.v[0], L.v[1], L.v[2], L.A1[0], L.A1[1], L.A1[2]);
-  return L.ns >= max_ns ? RT_RAY_MAXSTEPS : -1;
+  if (L.ns < max_ns) return -1;
+  hr = __builtin_nan("");  // out of steps inside the cloak: the residual here is not one at an exit
+  return RT_RAY_MAXSTEPS;
 }
 
 // Persistent integrator with in-line boundary events.
