@@ -2393,10 +2393,14 @@ int ws_reserve_for(Workspace &ws, const RenderJob &J) {
 // part of: the workspace belongs to the library.
 int upload_job(const RenderJob &J, const Workspace &ws, hipStream_t s) {
   hipStreamCaptureStatus cap = hipStreamCaptureStatusNone;
-  if (hipStreamIsCapturing(s, &cap) != hipSuccess || cap != hipStreamCaptureStatusNone) {
-    (void)hipGetLastError();
+  const hipError_t asked = hipStreamIsCapturing(s, &cap);
+  if (asked != hipSuccess) (void)hipGetLastError();
+  // Asked about the null stream while a stream ordered with it is captured
+  // somewhere, the runtime answers with this error; the null stream itself never
+  // is, and takes launches as ever.
+  const bool beside = asked == hipErrorStreamCaptureImplicit;
+  if ((asked != hipSuccess && !beside) || cap != hipStreamCaptureStatusNone)
     return fail(RT_E_DEVICE, "upload of camera records failed");
-  }
   const int n = (int)J.cams.size();
   if (n <= PUT_CAMS * PUT_LAUNCHES) {
     JobRecords r{};
