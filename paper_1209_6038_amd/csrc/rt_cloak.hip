@@ -2408,9 +2408,15 @@ int upload_job(const RenderJob &J, const Workspace &ws, hipStream_t s) {
     for (r.first = 0; r.first < n; r.first += PUT_CAMS) {
       r.n = std::min(PUT_CAMS, n - r.first);
       std::copy(J.cams.begin() + r.first, J.cams.begin() + r.first + r.n, r.cams);
-      hipLaunchKernelGGL(k_put_records, dim3(1), dim3(256), 0, s, r, ws.cams, ws.table);
+      // by this launch's own result: an error that the program left behind
+      // earlier does not keep the records, or a plan, from being made
+      CamP *dst = ws.cams;
+      float *table = ws.table;
+      void *args[] = {&r, &dst, &table};
+      const hipError_t e = hipLaunchKernel(reinterpret_cast<const void *>(k_put_records), dim3(1), dim3(256), args, 0, s);
+      if (e != hipSuccess) return fail(RT_E_DEVICE, "upload of camera records: %s", hipGetErrorString(e));
     }
-    return launch_err("upload of camera records");
+    return RT_OK;
   }
   if (hipMemcpyAsync(ws.cams, J.cams.data(), sizeof(CamP) * n, hipMemcpyHostToDevice, s) != hipSuccess ||
       hipMemcpyAsync(ws.table, J.table, sizeof(float) * TABLE_LEN, hipMemcpyHostToDevice, s) != hipSuccess ||

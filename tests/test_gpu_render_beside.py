@@ -1,5 +1,6 @@
 """GPU tests of render calls beside what the rest of a program does on the GPU:
-a capture that is under way on another stream."""
+a capture that is under way on another stream, and an error that an earlier
+call of the program left behind."""
 import ctypes
 import threading
 
@@ -56,3 +57,34 @@ def test_render_on_the_null_stream_beside_a_capture(flag, mode, thread):
     hip.hipStreamDestroy(stream)
     assert not failed and end == 0
     assert torch.equal(out, ref)
+
+
+def test_earlier_error_is_not_the_uploads():
+    """An error that a call of the program's own left behind neither refuses a
+    plan or a launch-shape search nor keeps a render from being made (which
+    reports it, as every call that checks its launches does)."""
+    import torch
+    from paper_1209_6038_amd import rt
+    say("case render after an earlier error")
+    hip = ctypes.CDLL("libamdhip64.so")
+    cl, cams, ref, out = _job()
+
+    def leave_error():
+        torch.cuda.synchronize()
+        p = ctypes.c_void_p()
+        assert hip.hipMalloc(ctypes.byref(p), ctypes.c_size_t(1 << 60)) != 0
+
+    try:
+        leave_error()
+        with pytest.raises(rt.RtError):
+            rt.render_multi(cl, W.render_opts(), W.room(), cams, 3, out=out)
+        leave_error()
+        plan = rt.RenderPlan(cl, W.render_opts(), W.room(), cams, 3)
+        leave_error()
+        rt.autotune_render(cl, W.render_opts(), W.room(), cams, 3)
+    finally:
+        hip.hipGetLastError()
+    plan.launch()
+    torch.cuda.synchronize()
+    assert torch.equal(out, ref) and torch.equal(plan.rgb, ref)
+    plan.close()
