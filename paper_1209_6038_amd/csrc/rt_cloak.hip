@@ -65,9 +65,14 @@ constexpr int LONG_RAY_ATTEMPTS = 64;      // see the issue priority in k_transi
 // when the CU's other SIMDs run it too (4 waves of one block, one lane each:
 // 2.6 us per azimuthal-e attempt, against 0.81 us with 16 lanes or more)
 constexpr int FEW_LANES = 16;
-// attempts between refills where the options leave it open: 2^20 random rays
-// 700, 650, 635 and 637 us at 2, 4, 8 and 12, two large frames 72.9 and 69.0 ms
-// at 2 and 12, the 3-D render 3.31 ms at 2 and 4, 3.38 at 8 and 12
+// attempts between refills where the options leave it open. At 2, 4, 8, 12 and
+// 16: the 3-D render (3.7 M entering rays) 3.23, 3.23, 3.25, 3.27 and 3.33 ms;
+// 64 views of 512^2 11.2, 10.8, 10.8, 10.7 and 10.9; one large frame 46.9, 45.9,
+// 46.2, 46.2 and 46.3; two of them in one launch 72.3, 70.0, 68.7, 68.4 and 68.3;
+// 2^20 random rays of the azimuthal-o branch 659, 650, 638, 626 and 637 us.
+// Launches whose longest ray sets the time (10^3 to 10^6 rays) differ by less
+// than 1%. 4 costs the largest launches 2% and the 3-D render nothing; the
+// launch-shape search finds the rest.
 constexpr int DEFAULT_REFILL = 4;
 constexpr int HOLD_SHARE = 64;             // see k_transit
 constexpr int DRAIN_PERIOD = 32;           // attempts between looks at the queue once it is exhausted
@@ -495,7 +500,9 @@ __global__ void __launch_bounds__(SORT_THREADS) k_sort_scatter(Table T) {
 // there through cold_args(), whose pointer the compiler cannot see through: a
 // wave's ~100 scalar registers do not hold the 40-odd pointers and constants
 // beside the tableau's coefficients, and values kept across the loop would be
-// spilled to vector lanes or push the coefficients out of their registers.
+// spilled to vector lanes or push the coefficients out of their registers. (The
+// DP45 variant still spills 121 scalars, 159 with weights: those that refills,
+// crossings and interfaces read; an attempt reads none of them.)
 struct TransitArgs {
   CloakP c;
   OptsP o;
@@ -864,9 +871,9 @@ __device__ __forceinline__ void run_segment(const CloakP &hot, const OptsP &hoto
     if (!any_lane(L.mode < M_IDLE)) return;
 
     // A wave that holds a ray past LONG_RAY_ATTEMPTS attempts is on the
-    // launch's critical path (the longest rays take ~1500 attempts where the
-    // mean is ~40): give it issue priority over the waves that share its
-    // SIMD, which fill the remaining issue slots.
+    // launch's critical path (the longest rays take thousands of attempts, next
+    // to r = a tens of thousands, where the mean is ~40): give it issue priority
+    // over the waves that share its SIMD, which fill the remaining issue slots.
     if (any_lane(L.mode < M_IDLE && L.ns > LONG_RAY_ATTEMPTS)) __builtin_amdgcn_s_setprio(3);
     else __builtin_amdgcn_s_setprio(0);
 
@@ -940,7 +947,11 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FRES ?
       kind[q] = (int)uniform(G.T.kind[(long long)q * G.T.cap]);
       // a ray's usual cost by branch: radial-o, radial-e, azimuthal-o,
       // azimuthal-e (DP45 attempts x instructions, ratios as measured over
-      // the 3-D render: 16, 31, 30 and 73 attempts)
+      // the 3-D render: 16, 31, 30 and 73 attempts). The fixed-step schemes
+      // take steps by path length, which these ratios do not follow; against
+      // equal shares they still take renders from 9.4 to 8.2 ms (4 views of
+      // 1024^2, RK4) and leave the Hamiltonian forms as they are, but 10^5
+      // mixed RK4 entries from 0.62 to 0.75.
       const unsigned int w = kind[q] == K_RO ? 1 : (kind[q] == K_AE ? 15 : 7);
       cost[q] = (unsigned long long)(sm.off[q + 1] - sm.off[q]) * w;
       total += cost[q];
@@ -963,6 +974,10 @@ __global__ void __launch_bounds__(256) __attribute__((amdgpu_waves_per_eu(FRES ?
   // and interfaces cost the wave ~30% more instructions per attempt, and the
   // SIMD-mates' instructions delay its own). Such a ray's path next to r = a
   // takes up to tens of thousands of attempts, which set the launch's length.
+  // All of this takes the chip for the launch's own. Beside another launch the
+  // SIMDs a wave was dealt may be taken: 18 launches of two large frames take
+  // 1,222 ms on one stream and 1,252 on two at block 128 (at 64 and 256, where
+  // one stream takes 1,247 and 1,240, the same on two).
   const unsigned int wave = uniform((blockIdx.x * blockDim.x + threadIdx.x) >> 6);
   const unsigned int nwave = gridDim.x * blockDim.x >> 6;
   const unsigned int round = min(nwave, (unsigned int)G.simds), rounds = nwave / round;

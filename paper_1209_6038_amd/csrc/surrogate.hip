@@ -91,13 +91,11 @@ int fail(int code, const char *fmt, ...) {
 // SiLU and its derivative with the hardware reciprocal (about 1 ulp): the
 // activations are rounded to BF16 or feed FP32 layers whose inputs carry
 // far more error than that, and an IEEE division would cost ~10
-// instructions per activation. Training and inference share these.
+// instructions per activation. Training and inference share these; the
+// derivative takes s = sigmoid(z), which its callers have.
 __device__ __forceinline__ float sigmoid_f(float z) { return __builtin_amdgcn_rcpf(1.0f + __expf(-z)); }
 __device__ __forceinline__ float silu_f(float z) { return z * sigmoid_f(z); }
-__device__ __forceinline__ float dsilu_f(float z) {
-  const float s = sigmoid_f(z);
-  return s * (1.0f + z * (1.0f - s));
-}
+__device__ __forceinline__ float dsilu_f(float z, float s) { return s * (1.0f + z * (1.0f - s)); }
 
 // ---------------------------------------------------------------------------
 // Target encoding. Entry (phi, z, alpha, beta) on r = b, exit (phi', z',
@@ -756,7 +754,8 @@ __global__ void __launch_bounds__(256) k_gate_idx(const float *__restrict__ x6, 
 // instructions and the SiLUs of 8 values per lane for each 32 inputs. Weights
 // come FDEPTH such groups ahead, across steps (1 to 3: 552, 540, 568 us).
 // 2^20 entries: 634 -> 540 us, 18 of them for the targets written from here
-// instead of by a launch of their own, 40 for the weights in operand order.
+// instead of by a launch of their own, 40 for the weights in operand order. It
+// uses all 256 registers and spills 10 (44 bytes of scratch per lane).
 // ---------------------------------------------------------------------------
 constexpr int FR = 128, FH = FR / 2, ALD = HID + 8, FDEPTH = 2;
 
@@ -958,8 +957,9 @@ __global__ void __launch_bounds__(256, 2) k_mlp_fused(const float *__restrict__ 
 //  3. k_grad_reduce: adds up both kernels' partial sums (fixed order, no
 //     atomics: the same batch gives the same gradient bit for bit).
 // One launch per layer product (FP32 pre-activations and both layouts of
-// every dz through HBM, 0.9 GB at 65,536 rows, 14 launches) took 440 us for a
-// gradient and step at 65,536 rows and 134 us at 1000; this takes 209 and 34.
+// every dz through HBM, 0.9 GB at 65,536 rows, 14 launches) took 446 us for a
+// gradient and step at 65,536 rows and 134 us at 1000; this takes 197 (173 when
+// one model's buffers stay in the last-level cache) and 34.
 // ---------------------------------------------------------------------------
 // columns of a block's row of partial sums: W1 and b1, b2, b3, then b4, W5, b5
 // (contiguous in the parameter vector each), and the loss's parts
@@ -1078,7 +1078,8 @@ __device__ __forceinline__ void store_tile(const bf16 *act, bf16 *__restrict__ d
 // instructions 54 (SiLU and its derivative, 5 exponentials and reciprocals
 // per unit and row); as 4 waves of 64 units with the weights loaded where
 // they are used, 250; with each operand read from LDS waited for (a product
-// 4400 clocks instead of 2700), 142.
+// 4400 clocks instead of 2700), 142. With 64 rows it uses all 256 registers and
+// spills 14 (60 bytes of scratch per lane), with 32 and 16 it uses 225 and 185.
 template <int NT>
 __global__ void __launch_bounds__(TRAIN_THREADS, 2) k_mlp_train(const float *__restrict__ x6, long long ld, int n,
                                                                 const float *__restrict__ P, const bf16 *Wt,
@@ -1185,7 +1186,7 @@ __global__ void __launch_bounds__(TRAIN_THREADS, 2) k_mlp_train(const float *__r
             for (int k = 0; k < NIN; ++k) z = fmaf(xr[tj][k], w1[k][r], z);
             const float s = sigmoid_f(z);
             pk[r] = (bf16)(z * s);
-            ds1[ti][tj][r] = pin(s * (1.0f + z * (1.0f - s)));
+            ds1[ti][tj][r] = pin(dsilu_f(z, s));
           }
           *reinterpret_cast<bf16x4 *>(&act[(16 * tj + c16) * ALD + u0]) = pk;
         }
@@ -1208,7 +1209,7 @@ __global__ void __launch_bounds__(TRAIN_THREADS, 2) k_mlp_train(const float *__r
           for (int r = 0; r < 4; ++r) {
             const float z = acc[ti][tj][r] + bias[r], s = sigmoid_f(z);
             pk[r] = (bf16)(z * s);
-            ds[ti][tj][r] = pin(s * (1.0f + z * (1.0f - s)));
+            ds[ti][tj][r] = pin(dsilu_f(z, s));
           }
           *reinterpret_cast<bf16x4 *>(&act[(16 * tj + c16) * ALD + u0]) = pk;
         }
@@ -1328,7 +1329,7 @@ __global__ void __launch_bounds__(TRAIN_THREADS, 2) k_mlp_train(const float *__r
               da = fmaf(dy[tj][o], w5[(r * NOUT + o) / 4][(r * NOUT + o) % 4], da);
               gw[o][r] = fmaf(a4, dy[tj][o], gw[o][r]);
             }
-            const float g = da * (s * (1.0f + z * (1.0f - s)));
+            const float g = da * dsilu_f(z, s);
             gz[r] += g;
             pk[tj][r] = (bf16)g;
           }
@@ -1782,14 +1783,15 @@ void forward_backward(rt_model mo, const float *x, const float *t, long long ld,
   // chain of layers takes 21, 25 and 35 us at 16, 32 and 64 rows and the work
   // beyond it shares the CU no better; past 8192 rows, 64, which read the
   // weights least often. Gradient and step at 4096 / 8192 / 16384 / 65536 rows,
-  // us: 44 / 59 / 90 / 276 with 16, 49 / 51 / 76 / 216 with 32, 60 / 61 / 71 /
-  // 196 with 64.
+  // one model's buffers, us: 41 / 54 / 84 / 257 with 16, 44 / 46 / 68 / 191 with
+  // 32, 52 / 54 / 65 / 173 with 64.
   const int rows = n <= 16 * TRAIN_BLOCKS ? 16 : n <= 32 * TRAIN_BLOCKS ? 32 : 64;
   const int blocks = std::min((int)gblocks(n, rows), TRAIN_BLOCKS);
   const auto kern = rows == 64 ? k_mlp_train<4> : rows == 32 ? k_mlp_train<2> : k_mlp_train<1>;
   hipLaunchKernelGGL(kern, dim3(blocks), dim3(TRAIN_THREADS), 0, s, x, ld, n, mo->P, mo->Pb, wr(mo), mo->scal,
                      job_for(mo, nullptr), ts);
-  // splits of at least two steps of 64 rows, two blocks per CU for large batches
+  // splits of two or more steps of 64 rows (the last takes what is left), two
+  // blocks per CU for large batches
   int splits = std::min(WG_SPLITS, std::max(1, n / (2 * WG_K)));
   const int kchunk = ((n + splits - 1) / splits + WG_K - 1) / WG_K * WG_K;
   splits = (n + kchunk - 1) / kchunk;
