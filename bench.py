@@ -92,14 +92,26 @@ ENTERED = (0, 2, 3, 4, 5)
 # known size (bench.py --copy-probe), per workload and launch shape (block,
 # refill period). Valid only for the integrator source it was measured on;
 # reported as null otherwise, or for a shape that was not measured.
-TRAFFIC = {"source_sha256": "ceb053584cfa29b26533f0ee6dafb23027c0f0a3031acff126b7182f62328b78",
+TRAFFIC = {"source_sha256": "f58512b4a1203a67cab911cbb00dffc346fb9372ce8ab3b151613c4da48c27e8",
            "bytes_per_launch": {
-               "orbit": {(64, 8): 17_285_255_325, (64, 12): 17_354_026_240, (64, 16): 17_395_528_465,
-                         (128, 8): 17_275_913_863, (128, 12): 17_353_971_687, (128, 16): 17_397_513_744,
-                         (256, 8): 17_168_934_619, (256, 12): 17_239_397_595, (256, 16): 17_283_679_932},
-               "render_1024": {(64, 2): 610_335_432, (64, 4): 608_493_981, (64, 8): 618_564_029,
-                               (128, 2): 605_033_310, (128, 4): 604_711_550, (128, 8): 611_586_348,
-                               (256, 2): 608_934_773, (256, 4): 605_956_284, (256, 8): 610_589_576}}}
+               "orbit": {(64, 1): 16_738_417_813, (64, 2): 17_009_632_832, (64, 4): 17_154_144_629,
+                         (64, 8): 17_279_727_413, (64, 12): 17_348_728_192, (64, 16): 17_397_468_256,
+                         (128, 1): 16_737_813_291, (128, 2): 16_990_783_936, (128, 4): 17_146_737_461,
+                         (128, 8): 17_273_762_496, (128, 12): 17_343_097_888, (128, 16): 17_395_099_808,
+                         (256, 1): 16_740_755_285, (256, 2): 16_975_301_515, (256, 4): 17_077_256_747,
+                         (256, 8): 17_168_847_776, (256, 12): 17_240_085_728, (256, 16): 17_282_412_437},
+               "render_1024": {(64, 1): 621_400_040, (64, 2): 611_462_040, (64, 4): 609_660_896,
+                               (64, 8): 613_459_320, (64, 12): 616_896_336, (64, 16): 616_571_792,
+                               (128, 1): 608_316_408, (128, 2): 606_892_656, (128, 4): 604_950_688,
+                               (128, 8): 611_743_864, (128, 12): 615_397_464, (128, 16): 617_224_088,
+                               (256, 1): 613_706_392, (256, 2): 609_376_056, (256, 4): 606_271_472,
+                               (256, 8): 610_391_088, (256, 12): 613_849_000, (256, 16): 614_846_976},
+               "batched": {(64, 1): 2_797_046_080, (64, 2): 2_776_216_720, (64, 4): 2_781_687_696,
+                           (64, 8): 2_800_361_432, (64, 12): 2_810_052_048, (64, 16): 2_812_950_368,
+                           (128, 1): 2_820_895_904, (128, 2): 2_809_033_312, (128, 4): 2_814_662_264,
+                           (128, 8): 2_825_209_864, (128, 12): 2_834_824_392, (128, 16): 2_839_514_024,
+                           (256, 1): 2_794_463_864, (256, 2): 2_768_956_432, (256, 4): 2_771_018_248,
+                           (256, 8): 2_786_994_456, (256, 12): 2_795_438_056, (256, 16): 2_799_165_632}}}
 
 
 def traffic_for(workload, shape=None):
