@@ -343,7 +343,7 @@ int rt_cloak_get_desc(rt_cloak cloak, rt_cloak_desc *out);
    inner_mirror; a ray whose axis bit has no handle is RT_RAY_INVALID.
    status: n int32 (RT_RAY_*); y5 is NaN for rays that did not leave.
    hres:   n floats or NULL, |v^T M v - 1| at the exit interface (NaN if the
-           ray never entered): the integrator's drift from the ray
+           ray never entered or ran out of steps): the integrator's drift from the ray
            Hamiltonian, which grows where it cannot resolve the path (entries
            with p_theta -> 0 pass next to the singular r = r1).
    nsteps: n int32 or NULL. r_out in opts is ignored. Errors as
